@@ -83,6 +83,30 @@ template <> struct Num<double> {
 // cell loads issued ahead of it.
 template <typename T> using glob = __attribute__((address_space(1))) T;
 
+// Element at a 32-bit byte offset (within one plane: at most 4096^2 doubles)
+// from a base that the whole workgroup shares.  The empty statements keep the
+// base in scalar registers and the offset in 32 bits (the compiler would add
+// the two first and carry a 64-bit vector address per variable), so that the
+// access takes no vector arithmetic.
+template <typename P> __device__ __forceinline__ P scalar_base(P p)
+{
+    asm("" : "+s"(p));
+    return p;
+}
+__device__ __forceinline__ uint32_t lane_offset(uint32_t off)
+{
+    asm("" : "+v"(off));
+    return off;
+}
+template <typename T> __device__ __forceinline__ T ld(const glob<T>* base, uint32_t off)
+{
+    return *(const glob<T>*)((const glob<char>*)scalar_base(base) + lane_offset(off));
+}
+template <typename T> __device__ __forceinline__ void st(glob<T>* base, uint32_t off, T x)
+{
+    *(glob<T>*)((glob<char>*)scalar_base(base) + lane_offset(off)) = x;
+}
+
 template <typename T> struct Phys {
     T g1inv, dginv, pi1, dpi;
     T eps;             // (12/13) x the WENO epsilon (the indicators' scale in weno5_cell)
@@ -244,54 +268,113 @@ __device__ __forceinline__ void weno3_cell(T b, T c, T d, T eps, T& lo, T& hi)
 // constant stencil returns the constant exactly, so where the stencils of a
 // whole wavefront are constant in those two variables their reconstruction
 // is skipped (same values, bit for bit).  ORD = 5 or 3 (WENO3 reads s[1..3]).
+//
+// edge_var: variable v (a constant after inlining) of the stencil s.
 template <typename T, int ND, int ORD>
-__device__ __forceinline__ void cell_edges(const Phys<T>& ph, const T (&s)[5][4 + ND],
-                                           T (&lo)[4 + ND], T (&hi)[4 + ND])
+__device__ __forceinline__ void edge_var(const Phys<T>& ph, int v, const T (&s)[5], T& lo, T& hi)
 {
     static_assert(ORD == 5 || ORD == 3, "WENO order");
     constexpr int NV = 4 + ND;
     constexpr int K0 = ORD == 5 ? 0 : 1, K1 = ORD == 5 ? 5 : 4;   // stencil cells read
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        if (v == 1 || v == NV - 1) {
-            // constant stencil across the wavefront: the edges are the cell
-            // value, which every check below would keep as well
-            const bool flat = (ORD == 3 || s[0][v] == s[2][v]) && s[1][v] == s[2][v] && s[3][v] == s[2][v] &&
-                              (ORD == 3 || s[4][v] == s[2][v]);
-            if (__all(flat)) {
-                lo[v] = s[2][v];
-                hi[v] = s[2][v];
-                continue;
-            }
-        }
-        if (ORD == 5)
-            weno5_cell<T>(s[0][v], s[1][v], s[2][v], s[3][v], s[4][v], ph.eps, lo[v], hi[v]);
-        else
-            weno3_cell<T>(s[1][v], s[2][v], s[3][v], ph.eps3, lo[v], hi[v]);
-        if (v < 2) {
-            T big = v == 0 ? ph.rho1 : ph.rho2;
-#pragma unroll
-            for (int k = K0; k < K1; ++k) big = fmax(big, fabs(s[k][v]));
-            const T tol = -Num<T>::round_tol * big;
-            const T mid = ORD == 5 ? (T(12) * s[2][v] - lo[v] - hi[v]) * T(0.1)
-                                   : (T(6) * s[2][v] - lo[v] - hi[v]) * T(0.25);
-            const bool keep = (lo[v] >= tol) && (hi[v] >= tol) && (mid >= tol);
-            lo[v] = keep ? lo[v] : s[2][v];
-            hi[v] = keep ? hi[v] : s[2][v];
-        } else if (v == NV - 1) {
-            const T lb = -Num<T>::round_tol, ub = T(1) + Num<T>::round_tol;
-            const T mid = ORD == 5 ? (T(12) * s[2][v] - lo[v] - hi[v]) * T(0.1)
-                                   : (T(6) * s[2][v] - lo[v] - hi[v]) * T(0.25);
-            const bool keep = (lo[v] >= lb) && (lo[v] <= ub) && (hi[v] >= lb) && (hi[v] <= ub) && (mid >= lb) && (mid <= ub);
-            lo[v] = keep ? lo[v] : s[2][v];
-            hi[v] = keep ? hi[v] : s[2][v];
+    const T c = s[2];
+    if (v == 1 || v == NV - 1) {
+        // constant stencil across the wavefront: the edges are the cell
+        // value, which every check below would keep as well
+        const bool flat = (ORD == 3 || s[0] == c) && s[1] == c && s[3] == c && (ORD == 3 || s[4] == c);
+        if (__all(flat)) {
+            lo = c;
+            hi = c;
+            return;
         }
     }
-    const T cl = (ph.gamma(lo[3 + ND]) + T(1)) * lo[2 + ND] + ph.pinf(lo[3 + ND]);
-    const T ch = (ph.gamma(hi[3 + ND]) + T(1)) * hi[2 + ND] + ph.pinf(hi[3 + ND]);
-    if (!((cl > T(0)) && (ch > T(0)))) {
+    if constexpr (ORD == 5)
+        weno5_cell<T>(s[0], s[1], c, s[3], s[4], ph.eps, lo, hi);
+    else
+        weno3_cell<T>(s[1], c, s[3], ph.eps3, lo, hi);
+    if (v < 2 || v == NV - 1) {
+        const T mid = ORD == 5 ? (T(12) * c - lo - hi) * T(0.1) : (T(6) * c - lo - hi) * T(0.25);
+        const T least = fmin(fmin(lo, hi), mid);
+        if (v < 2) {
+            // the tolerance is looked up only where some lane is below zero
+            if (!__all(least >= T(0))) {
+                T big = v == 0 ? ph.rho1 : ph.rho2;
 #pragma unroll
-        for (int v = 0; v < NV; ++v) { lo[v] = s[2][v]; hi[v] = s[2][v]; }
+                for (int k = K0; k < K1; ++k) big = fmax(big, fabs(s[k]));
+                const bool keep = least >= -Num<T>::round_tol * big;
+                lo = keep ? lo : c;
+                hi = keep ? hi : c;
+            }
+        } else {
+            const T most = fmax(fmax(lo, hi), mid);
+            const bool keep = least >= -Num<T>::round_tol && most <= T(1) + Num<T>::round_tol;
+            lo = keep ? lo : c;
+            hi = keep ? hi : c;
+        }
+    }
+}
+
+// (Gamma+1) p + Pi > 0 at both edges
+template <typename T>
+__device__ __forceinline__ bool edges_have_c2(const Phys<T>& ph, T a2l, T a2h, T pl, T phi)
+{
+    const T cl = (ph.gamma(a2l) + T(1)) * pl + ph.pinf(a2l);
+    const T ch = (ph.gamma(a2h) + T(1)) * phi + ph.pinf(a2h);
+    return (cl > T(0)) && (ch > T(0));
+}
+
+// all variables of a stencil in registers
+template <typename T, int ND, int ORD>
+__device__ __forceinline__ void cell_edges(const Phys<T>& ph, const T (&q)[5][4 + ND],
+                                           T (&lo)[4 + ND], T (&hi)[4 + ND])
+{
+    constexpr int NV = 4 + ND;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const T s[5] = { q[0][v], q[1][v], q[2][v], q[3][v], q[4][v] };
+        edge_var<T, ND, ORD>(ph, v, s, lo[v], hi[v]);
+    }
+    if (!edges_have_c2(ph, lo[3 + ND], hi[3 + ND], lo[2 + ND], hi[2 + ND])) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) { lo[v] = q[2][v]; hi[v] = q[2][v]; }
+    }
+}
+
+// One variable at a time from LDS to LDS (the x-y edge tasks): cell k of the
+// stencil of variable v at w[v * wv + k * stride], edges to em/ep[v * es].
+// Only a2 and p, which the last check reads, stay in registers; the stencil
+// of the next variable is read while one is reconstructed.  (With all 5 x NV
+// values read first the compiler keeps them: 25 more registers in float, 50
+// in double, across the reconstruction.)
+template <typename T, int ND, int ORD>
+__device__ __forceinline__ void cell_edges_lds(const Phys<T>& ph, const T* w, int wv, int stride, T* em, T* ep, int es)
+{
+    constexpr int NV = 4 + ND;
+    constexpr int K0 = ORD == 5 ? 0 : 1, K1 = ORD == 5 ? 5 : 4;
+    T st[2][5];
+    auto fetch = [&](int v, T (&s)[5]) {
+#pragma unroll
+        for (int k = K0; k < K1; ++k) s[k] = w[v * wv + k * stride];
+    };
+    T a2l, a2h, pl, phi;
+    fetch(NV - 1, st[0]);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int v = NV - 1 - i;                     // a2, p, then the others
+        if (i + 1 < NV) fetch(v - 1, st[(i + 1) & 1]);
+        T lo, hi;
+        edge_var<T, ND, ORD>(ph, v, st[i & 1], lo, hi);
+        em[v * es] = lo;
+        ep[v * es] = hi;
+        if (i == 0) { a2l = lo; a2h = hi; }
+        if (i == 1) { pl = lo; phi = hi; }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (!edges_have_c2(ph, a2l, a2h, pl, phi)) {
+        for (int v = 0; v < NV; ++v) {
+            const T c = w[v * wv + 2 * stride];
+            em[v * es] = c;
+            ep[v * es] = c;
+        }
     }
 }
 
@@ -299,41 +382,46 @@ __device__ __forceinline__ void cell_edges(const Phys<T>& ph, const T (&s)[5][4 
 // is a2_K u_f where u_f is the face velocity of the HLLC flux of a passive
 // scalar (Johnsen-Colonius adaptation).  f[0..NV-2]: fluxes of (a1r1, a2r2,
 // momenta, Et); f[NV-1]: a2 flux; f[NV]: u_f.  The flux of E is
-// f[NV-2] + Pi(a2_K) u_f.
+// f[NV-2] + Pi(a2_K) u_f.  Only the side that enters has its energy
+// computed.
+//
+// (The star flux with Q* put in, u_f = chi S* and so on, takes 80 operations
+// a face against 130 and cancels nothing, but the rounding of S_K (chi - 1)
+// here, 1e-4 m/s in float, is what the low pressures of a solve carry: 3e-5
+// of them in two steps, and 1e-9 to 1e-5 of a double solve's sensor.  With
+// other forms of the flux or of the reconstruction the results are other
+// numbers by that much.)
 template <typename T, int ND, int DIR>
 __device__ __forceinline__ void hllc(const Phys<T>& ph, const T (&wl)[4 + ND], const T (&wr)[4 + ND],
                                      T (&f)[5 + ND])
 {
     constexpr int NV = 4 + ND;
-    T rl = wl[0] + wl[1], rr = wr[0] + wr[1];
-    T ul = wl[2 + DIR], ur = wr[2 + DIR];
-    T pl = wl[2 + ND], pr = wr[2 + ND];
-    T gl = ph.gamma(wl[3 + ND]), gr = ph.gamma(wr[3 + ND]);
-    T Pl = ph.pinf(wl[3 + ND]), Pr = ph.pinf(wr[3 + ND]);
-    T kel = T(0), ker = T(0);
-#pragma unroll
-    for (int m = 0; m < ND; ++m) { kel += wl[2 + m] * wl[2 + m]; ker += wr[2 + m] * wr[2 + m]; }
-    // energies without Pi (its flux Pi(a2_K) u_f is added by the caller's source)
-    T El = gl * pl + T(0.5) * rl * kel;
-    T Er = gr * pr + T(0.5) * rr * ker;
-    T cl = Num<T>::sqrt_ratio((gl + T(1)) * pl + Pl, gl * rl);
-    T cr = Num<T>::sqrt_ratio((gr + T(1)) * pr + Pr, gr * rr);
-    T sl = fmin(ul - cl, ur - cr);
-    T sr = fmax(ul + cl, ur + cr);
-    T ml = rl * (sl - ul), mr = rr * (sr - ur);
-    T ss = (pr - pl + ml * ul - mr * ur) * Num<T>::rcp(ml - mr);
+    const T rl = wl[0] + wl[1], rr = wr[0] + wr[1];
+    const T ul = wl[2 + DIR], ur = wr[2 + DIR];
+    const T pl = wl[2 + ND], pr = wr[2 + ND];
+    const T gl = ph.gamma(wl[3 + ND]), gr = ph.gamma(wr[3 + ND]);
+    const T Pl = ph.pinf(wl[3 + ND]), Pr = ph.pinf(wr[3 + ND]);
+    const T cl = Num<T>::sqrt_ratio((gl + T(1)) * pl + Pl, gl * rl);
+    const T cr = Num<T>::sqrt_ratio((gr + T(1)) * pr + Pr, gr * rr);
+    const T sl = fmin(ul - cl, ur - cr);
+    const T sr = fmax(ul + cl, ur + cr);
+    const T ml = rl * (sl - ul), mr = rr * (sr - ur);
+    const T ss = (pr - pl + ml * ul - mr * ur) * Num<T>::rcp(ml - mr);
     // side whose (star) state enters: left if S_L >= 0 or S* >= 0
     const bool left = (sl >= T(0)) || (ss >= T(0));
     const T sK = left ? sl : sr;
-    const T sk = left ? fmin(sl, T(0)) : fmax(sr, T(0));   // 0 for the upwind fluxes
+    const bool star = left ? sl < T(0) : sr > T(0);        // else the upwind flux
     T w[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) w[v] = left ? wl[v] : wr[v];
     const T rho = left ? rl : rr;
-    const T un = left ? ul : ur;
-    const T p = left ? pl : pr;
-    const T E = left ? El : Er;
-    const bool star = sk != T(0);
+    const T un = w[2 + DIR], p = w[2 + ND];
+    T ke = T(0);
+#pragma unroll
+    for (int m = 0; m < ND; ++m) ke += w[2 + m] * w[2 + m];
+    // energy without Pi (its flux Pi(a2_K) u_f is added by the caller's source)
+    const T E = Num<T>::fma(T(0.5) * rho, ke, (left ? gl : gr) * p);
+    const T sk = star ? sK : T(0);                     // 0 for the upwind fluxes
     const T rs = star ? Num<T>::rcp(sK - ss) : T(0);
     const T chi = star ? (sK - un) * rs : T(1);
     f[0] = w[0] * un;
@@ -537,22 +625,48 @@ constexpr int round_up64(int x) { return (x + 63) / 64 * 64; }
 // wavefronts (threads past the last cell help with the x-y tasks only).
 template <int TX, int TY> constexpr int stage_threads() { return round_up64(TX * TY); }
 
-// Occupancy target of the stage kernel: three wavefronts per SIMD for the
-// float kernels (at most 168 VGPRs), two for double (at most 256 VGPRs; the
-// split x-y pass below keeps a 16 x 8 tile's LDS under a quarter of the CU's).
-template <typename T> constexpr int stage_waves_per_eu() { return sizeof(T) == 4 ? 3 : 2; }
-
-// The x-y part of a plane in one pass (float: the edges of both axes live in
-// LDS at once, then all faces) or split by axis (double: the x edges, x faces
-// and x sums, then the same for y, each axis's face fluxes written over its
-// own edges after a barrier), which needs about half the LDS for the edges.
-template <typename T> constexpr bool stage_split_xy() { return sizeof(T) == 8; }
+// How a stage kernel is laid out, by type, RK stage and WENO order.
+//   split  the x-y part of a plane split by axis (the x edges, x faces and x
+//          sums, then the same for y, each axis's face fluxes written over
+//          its own edges after a barrier): 30 KB of LDS for a float 16 x 16
+//          tile against 51 KB, for four more barriers a plane
+//   waves  wavefronts per SIMD the registers are held to
+//   early  the cell's U and dU are loaded before the x-y work of its plane
+//          (their latency hides under it) instead of after
+//   late   the next plane's halo cells are loaded after the z edges of this
+//          one and converted at the end of the iteration (their latency hides
+//          under the z face and the update) instead of loaded where they are
+//          converted
+// Measured launches (us; start of this layout / the others tried):
+//   float WENO5, 256^3: stages 1, 2 without a spill, so they take every load
+//     ahead: 963, 999 (without late: 980, 1038; split at 4 waves: 965, 1029).
+//     Stage 3 carries the reduction (16 registers and its doubles); with
+//     either load ahead it spills: 1077 (early: 1136; both: 1274;
+//     split: 1270).
+//   float WENO3, 150^3: less work between barriers and fewer registers, so a
+//     fourth wavefront pays: 200, 216, 262 (joint at 3: 225, 256, 279).
+//   double, 192^3: LDS for two axes' edges would halve the occupancy; where
+//     it fits 256 registers, the cell's own loads go ahead: 881, 918, 994
+//     (none early: 910, 944, 994; late: 889, 932, 1098; both: 904, 1022,
+//     1223; three waves spill: 1400, 1610, 1853).
+struct StageLayout {
+    bool split;
+    int waves;
+    bool early, late;
+};
+template <typename T, int ND, int STAGE, int ORD> constexpr StageLayout stage_layout()
+{
+    if (sizeof(T) == 8) return { true, 2, STAGE < 2, false };
+    if (ND < 3) return { false, 3, false, false };
+    if (ORD == 3) return { true, 4, false, false };
+    return STAGE < 2 ? StageLayout{ false, 3, true, true } : StageLayout{ false, 4, false, false };
+}
 
 // RK stage STAGE = 0, 1, 2 (compiled separately: only the last carries the
 // reduction, only the first skips dU); WENO order ORD = 5 or 3.
 template <typename T, int ND, int TX, int TY, int STAGE, int ORD>
 __global__ void __launch_bounds__((stage_threads<TX, TY>()))
-__attribute__((amdgpu_waves_per_eu(stage_waves_per_eu<T>())))
+__attribute__((amdgpu_waves_per_eu(stage_layout<T, ND, STAGE, ORD>().waves)))
 stage_kernel(LaunchArgs a)
 {
     constexpr int NV = 4 + ND;
@@ -576,7 +690,8 @@ stage_kernel(LaunchArgs a)
     constexpr int AL = WSZ > FSZ ? WSZ : FSZ;          // W plane and face fluxes share LDS
     // split pass: edge tasks of one axis at a time; an axis's face fluxes
     // ((NV+1) x its faces <= 2 NV x its edge tasks) overwrite its edges
-    constexpr bool SPLIT = stage_split_xy<T>();
+    constexpr bool SPLIT = stage_layout<T, ND, STAGE, ORD>().split;
+    constexpr bool EARLY = stage_layout<T, ND, STAGE, ORD>().early, LATE = stage_layout<T, ND, STAGE, ORD>().late;
     constexpr int ESX = EXN > EYN ? EXN : EYN;
     constexpr int EST = SPLIT ? ESX : ES;              // stride of the edge arrays
     static_assert(!SPLIT || ((NV + 1) * FXN <= 2 * NV * ESX && (NV + 1) * FYN <= 2 * NV * ESX), "face alias");
@@ -598,8 +713,8 @@ stage_kernel(LaunchArgs a)
     if (wi >= a.n_work) return;
     const WorkItem item = a.work[wi];
     const SampleDesc& d = a.desc[item.sample];
-    SampleState* st = a.state + item.sample;
-    if (st->done) return;
+    SampleState* state = a.state + item.sample;
+    if (state->done) return;
 
     const Phys<T> ph(a.ph);
     const int n = d.n;
@@ -617,7 +732,7 @@ stage_kernel(LaunchArgs a)
     const glob<T>* __restrict__ ua = (const glob<T>*)d.buf[a.src];
     glob<T>* __restrict__ ub = (glob<T>*)d.buf[a.src ^ 1];
     glob<T>* __restrict__ du = (glob<T>*)d.du;
-    const T dt = (T)st->dt;
+    const T dt = (T)state->dt;
     const T ih = (T)(1.0 / d.h);
     constexpr int stage = STAGE;
     const T rkA = (T)c_rk_a[stage], rkB = (T)c_rk_b[stage];
@@ -627,70 +742,55 @@ stage_kernel(LaunchArgs a)
     red.init();
 
     const T beta = (T)(kFarFieldSigma * d.h);     // far-field relaxation fraction
-    // load plane gz (with halo) into sW as primitives
-    // A plane with its halo in two parts: the loads of this thread's cells of
-    // it (at most PK) into registers, and their conversion into sW.  In
-    // the 3-D float first stage the loads of plane p+1 are issued before the
-    // x-y work of plane p and converted at plane p+1, so that their latency
-    // hides under that work (the other stages and double have no registers
-    // to spare: they would spill).
+    // Plane gz with its halo into sW as primitives: the loads of this
+    // thread's cells of it (at most PK), and their conversion.
     constexpr int PK = (HX * HY + NT - 1) / NT;
-    constexpr bool PREFETCH = ND == 3 && sizeof(T) == 4 && STAGE == 0;
-    auto plane_fetch = [&](int gz, T (&pf)[PK][NV]) {
-        const int64_t zoff = (int64_t)bc_map(gz, ND == 3 ? n : 1, bc) * plane;
+        // In-plane offsets of this thread's halo cells, the same for every plane
+    uint32_t hidx[PK];
 #pragma unroll
-        for (int k = 0; k < PK; ++k) {
-            const int e = tid + k * NT;
-            if (e < HX * HY) {
-                const int hy = e / HX, hx = e % HX;
-                const int cx = bc_map(x0 + hx - 3, n, bc);
-                const int cy = ND >= 2 ? bc_map(y0 + hy - 3, n, bc) : 0;
-                const int64_t idx = zoff + (int64_t)cy * n + cx;
-#pragma unroll
-                for (int v = 0; v < NV; ++v) pf[k][v] = ua[v * ncell + idx];
-            }
+    for (int k = 0; k < PK; ++k) {
+        const int e = tid + k * NT;
+        const int cx = bc_map(x0 + e % HX - 3, n, bc);
+        const int cy = ND >= 2 ? bc_map(y0 + e / HX - 3, n, bc) : 0;
+        hidx[k] = (uint32_t)(cy * n + cx) * (uint32_t)sizeof(T);
+    }
+    auto halo_cell = [&](int k, const T (&q)[NV]) {
+        const int e = tid + k * NT;
+        T w[NV];
+        to_prim<T, ND>(ph, q, w);
+        if (bc == OFM_BC_CHARACTERISTIC) {
+            // ghosts outside one domain side (corner ghosts are never read)
+            const int rx = x0 + e % HX - 3, ry = ND >= 2 ? y0 + e / HX - 3 : 0;
+            const bool ox = rx < 0 || rx >= n, oy = ND >= 2 && (ry < 0 || ry >= n);
+            if (ox != oy) char_ghost<T, ND>(ph, w, ox ? 0 : 1, (ox ? rx : ry) < 0 ? -1 : 1, beta);
         }
+#pragma unroll
+        for (int v = 0; v < NV; ++v) sW[v * HY * HX + e] = w[v];
+    };
+    auto plane_fetch = [&](int gz, T (&pf)[PK][NV]) {
+        const glob<T>* z = ua + (int64_t)bc_map(gz, ND == 3 ? n : 1, bc) * plane;
+#pragma unroll
+        for (int k = 0; k < PK; ++k)
+            if (tid + k * NT < HX * HY)
+#pragma unroll
+                for (int v = 0; v < NV; ++v) pf[k][v] = ld<T>(z + v * ncell, hidx[k]);
     };
     auto plane_store = [&](const T (&pf)[PK][NV]) {
 #pragma unroll
-        for (int k = 0; k < PK; ++k) {
-            const int e = tid + k * NT;
-            if (e < HX * HY) {
-                const int hy = e / HX, hx = e % HX;
-                const int rx = x0 + hx - 3, ry = ND >= 2 ? y0 + hy - 3 : 0;
-                T w[NV];
-                to_prim<T, ND>(ph, pf[k], w);
-                if (bc == OFM_BC_CHARACTERISTIC) {
-                    // ghosts outside one domain side (corner ghosts are never read)
-                    const bool ox = rx < 0 || rx >= n, oy = ND >= 2 && (ry < 0 || ry >= n);
-                    if (ox != oy) char_ghost<T, ND>(ph, w, ox ? 0 : 1, (ox ? rx : ry) < 0 ? -1 : 1, beta);
-                }
-#pragma unroll
-                for (int v = 0; v < NV; ++v) sW[(v * HY + hy) * HX + hx] = w[v];
-            }
-        }
+        for (int k = 0; k < PK; ++k)
+            if (tid + k * NT < HX * HY) halo_cell(k, pf[k]);
     };
     // without prefetch: one cell at a time (fewer registers live at once)
     auto load_plane = [&](int gz) {
-        const int64_t zoff = (int64_t)bc_map(gz, ND == 3 ? n : 1, bc) * plane;
-        for (int e = tid; e < HX * HY; e += NT) {
-            const int hy = e / HX, hx = e % HX;
-            const int rx = x0 + hx - 3, ry = ND >= 2 ? y0 + hy - 3 : 0;
-            const int cx = bc_map(rx, n, bc);
-            const int cy = ND >= 2 ? bc_map(ry, n, bc) : 0;
-            const int64_t idx = zoff + (int64_t)cy * n + cx;
-            T q[NV], w[NV];
+        const glob<T>* z = ua + (int64_t)bc_map(gz, ND == 3 ? n : 1, bc) * plane;
 #pragma unroll
-            for (int v = 0; v < NV; ++v) q[v] = ua[v * ncell + idx];
-            to_prim<T, ND>(ph, q, w);
-            if (bc == OFM_BC_CHARACTERISTIC) {
-                // ghosts outside one domain side (corner ghosts are never read)
-                const bool ox = rx < 0 || rx >= n, oy = ND >= 2 && (ry < 0 || ry >= n);
-                if (ox != oy) char_ghost<T, ND>(ph, w, ox ? 0 : 1, (ox ? rx : ry) < 0 ? -1 : 1, beta);
+        for (int k = 0; k < PK; ++k)
+            if (tid + k * NT < HX * HY) {
+                T q[NV];
+#pragma unroll
+                for (int v = 0; v < NV; ++v) q[v] = ld<T>(z + v * ncell, hidx[k]);
+                halo_cell(k, q);
             }
-#pragma unroll
-            for (int v = 0; v < NV; ++v) sW[(v * HY + hy) * HX + hx] = w[v];
-        }
     };
 
     // split x-y pass, one axis (DIR = 0: x, 1: y): edges of the axis's tasks
@@ -712,14 +812,7 @@ stage_kernel(LaunchArgs a)
                 base = (cy + 1) * HX + col + 3;
                 stride = HX;
             }
-            T st[5][NV], lo[NV], hi[NV];
-#pragma unroll
-            for (int k = 0; k < 5; ++k)
-#pragma unroll
-                for (int v = 0; v < NV; ++v) st[k][v] = sW[v * HY * HX + base + k * stride];
-            cell_edges<T, ND, ORD>(ph, st, lo, hi);
-#pragma unroll
-            for (int v = 0; v < NV; ++v) { sEm[v * EST + e] = lo[v]; sEp[v * EST + e] = hi[v]; }
+            cell_edges_lds<T, ND, ORD>(ph, sW + base, HY * HX, stride, sEm + e, sEp + e, EST);
         }
         __syncthreads();
         T fa[NV + 1], fb[NV + 1];
@@ -782,14 +875,7 @@ stage_kernel(LaunchArgs a)
             const int cy = f / TX - 1, col = f % TX;                  // y task
             const int base = isx ? (row + (ND >= 2 ? 3 : 0)) * HX + cx + 1 : (cy + 1) * HX + col + 3;
             const int stride = isx ? 1 : HX;
-            T s[5][NV], lo[NV], hi[NV];
-#pragma unroll
-            for (int k = 0; k < 5; ++k)
-#pragma unroll
-                for (int v = 0; v < NV; ++v) s[k][v] = sW[v * HY * HX + base + k * stride];
-            cell_edges<T, ND, ORD>(ph, s, lo, hi);
-#pragma unroll
-            for (int v = 0; v < NV; ++v) { sEm[v * ES + e] = lo[v]; sEp[v * ES + e] = hi[v]; }
+            cell_edges_lds<T, ND, ORD>(ph, sW + base, HY * HX, stride, sEm + e, sEp + e, ES);
         }
         __syncthreads();
         // faces: x faces i-1/2 (i = 0..TX) of every row, y faces j-1/2
@@ -855,18 +941,17 @@ stage_kernel(LaunchArgs a)
     if (ND >= 2) dxy2 = add_dist2(dxy2, axis_dist2(d.centre[1], gy, n_d));
 
     // the low-storage RK stage of one cell, given its U and dU
-    auto update = [&](int64_t idx, const T (&L)[NV], const T (&uo)[NV], const T (&duo)[NV], double d2) {
+    auto update = [&](int64_t zoff, uint32_t col, const T (&L)[NV], const T (&uo)[NV], const T (&duo)[NV], double d2) {
         T qn[NV];
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
-            const int64_t o = v * ncell + idx;
             T dv = dt * L[v];
             if constexpr (stage > 0) dv += rkA * duo[v];
-            if constexpr (stage < 2) du[o] = dv;
+            if constexpr (stage < 2) st<T>(du + (v * ncell + zoff), col, dv);
             qn[v] = uo[v] + rkB * dv;
-            ub[o] = qn[v];
+            st<T>(ub + (v * ncell + zoff), col, qn[v]);
         }
-        if constexpr (stage == 2) reduce_cell<T, ND>(a.ph, d, qn, idx, d2, red);
+        if constexpr (stage == 2) reduce_cell<T, ND>(a.ph, d, qn, zoff + col / (uint32_t)sizeof(T), d2, red);
     };
 
     if constexpr (ND <= 2) {
@@ -878,15 +963,15 @@ stage_kernel(LaunchArgs a)
         for (int v = 0; v < NV; ++v) wc[v] = sW[(v * HY + ty + (ND >= 2 ? 3 : 0)) * HX + tx + 3];
         plane_xy(xy);
         if (mine) {
-            const int64_t idx = (ND == 2 ? (int64_t)gy * n : 0) + gx;
+            const uint32_t col = (uint32_t)((ND == 2 ? gy * n : 0) + gx) * (uint32_t)sizeof(T);
             T L[NV], uo[NV], duo[NV];
             rate(xy, wc, L);
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
-                uo[v] = ua[v * ncell + idx];
-                duo[v] = stage > 0 ? du[v * ncell + idx] : T(0);
+                uo[v] = ld<T>(ua + v * ncell, col);
+                duo[v] = stage > 0 ? ld<T>(du + v * ncell, col) : T(0);
             }
-            update(idx, L, uo, duo, dxy2);
+            update(0, col, L, uo, duo, dxy2);
         }
     } else {
         // z: each thread keeps the primitives of its own column, planes
@@ -896,51 +981,41 @@ stage_kernel(LaunchArgs a)
         const int z0 = tzc * a.zchunk;
         const int z1 = min(z0 + a.zchunk, n) - 1;      // last plane of the chunk
         const int cxg = min(gx, n - 1), cyg = min(gy, n - 1);
-        const int64_t col = (int64_t)cyg * n + cxg;    // (clamped) column of this thread
+        const uint32_t col = (uint32_t)(cyg * n + cxg) * (uint32_t)sizeof(T);   // (clamped) column of this thread
         T q[5][NV];                                    // primitives of planes p-1..p+3
-        T pf[PK][NV];                                  // this thread's cells of the next plane (prefetch)
+        T pf[PK][NV];                                  // this thread's halo cells of the next plane (LATE)
         T ep[NV];                                      // upper z edge of cell p
         T fz_lo[NV + 1];                               // flux through face p-1/2
         // One loop body does all the work (so that every edge and face is
         // computed by the same code whatever the chunking, bit for bit):
         // p = z0-6..z0-3 only fill the queue, p = z0-2 adds the edges of
         // cell z0-1, p = z0-1 the face z0-1/2, and p >= z0 the x-y work of
-        // plane p and the update of cell p.
+        // plane p and the update of cell p.  Plane p is converted into sW at
+        // the end of iteration p-1.
         for (int p = z0 - 6; p <= z1; ++p) {
             const bool xy_work = p >= z0;
             // global loads issued before the x-y work: the column's plane
-            // p+3 and this cell's U and dU
-            const int64_t inext = (int64_t)bc_map(p + 3, n, bc) * plane + col;
-            const int64_t icell = (int64_t)p * plane + col;
-            // (in double, U and dU are loaded after the x-y work instead: 28
-            // more registers across it would halve the occupancy)
-            constexpr bool early = sizeof(T) == 4;
+            // p+3 and, if EARLY, this cell's U and dU
+            const int64_t znext = (int64_t)bc_map(p + 3, n, bc) * plane;
+            const int64_t zcell = (int64_t)p * plane;
             T qn[NV], uo[NV], duo[NV];
             auto load_cell = [&]() {
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
-                    uo[v] = ua[v * ncell + icell];
-                    duo[v] = stage > 0 ? du[v * ncell + icell] : T(0);
+                    uo[v] = ld<T>(ua + (v * ncell + zcell), col);
+                    duo[v] = stage > 0 ? ld<T>(du + (v * ncell + zcell), col) : T(0);
                 }
             };
 #pragma unroll
-            for (int v = 0; v < NV; ++v) qn[v] = ua[v * ncell + inext];
-            if (early && xy_work) load_cell();
+            for (int v = 0; v < NV; ++v) qn[v] = ld<T>(ua + (v * ncell + znext), col);
+            if (EARLY && xy_work) load_cell();
             T xy[NV + 1];
             if (xy_work) {
-                if constexpr (!SPLIT) __syncthreads();   // sW is the joint pass's face-flux area
-                if constexpr (PREFETCH) {
-                    plane_store(pf);                     // plane p, loaded one plane ahead
-                    if (p < z1) plane_fetch(p + 1, pf);
-                } else {
-                    load_plane(p);
-                }
                 __syncthreads();
                 plane_xy(xy);
-                if (!early) load_cell();
-            } else if (PREFETCH && p == z0 - 1) {
-                plane_fetch(z0, pf);
+                if (!EARLY) load_cell();
             }
+            const bool more = p >= z0 - 1 && p < z1;               // plane p+1 is wanted
 #pragma unroll
             for (int k = 0; k < 4; ++k)
 #pragma unroll
@@ -951,6 +1026,10 @@ stage_kernel(LaunchArgs a)
             if (p >= z0 - 2) {
                 T lo[NV], hi[NV];
                 cell_edges<T, ND, ORD>(ph, q, lo, hi);             // cell p+1
+                if (LATE && more) {
+                    __builtin_amdgcn_sched_barrier(0);             // not ahead of the z edges' registers
+                    plane_fetch(p + 1, pf);
+                }
                 if (p >= z0 - 1) {
                     T fz[NV + 1];
                     hllc<T, ND, ND - 1>(ph, ep, lo, fz);           // face p+1/2
@@ -960,13 +1039,17 @@ stage_kernel(LaunchArgs a)
                         for (int v = 0; v < NV; ++v) sum[v] = xy[v] + (fz_lo[v] - fz[v]);
                         sum[NV] = xy[NV] + (fz[NV] - fz_lo[NV]);
                         rate(sum, q[1], L);
-                        update(icell, L, uo, duo, stage == 2 ? add_dist2(dxy2, axis_dist2(d.centre[2], p, n_d)) : 0.0);
+                        update(zcell, col, L, uo, duo, stage == 2 ? add_dist2(dxy2, axis_dist2(d.centre[2], p, n_d)) : 0.0);
                     }
 #pragma unroll
                     for (int v = 0; v <= NV; ++v) fz_lo[v] = fz[v];
                 }
 #pragma unroll
                 for (int v = 0; v < NV; ++v) ep[v] = hi[v];
+            }
+            if (more) {
+                if constexpr (!SPLIT) __syncthreads();   // sW is the joint pass's face-flux area
+                if constexpr (LATE) plane_store(pf); else load_plane(p + 1);
             }
         }
     }

@@ -97,6 +97,22 @@ def test_fp64_cloud_100_steps(ctx, cloud, n):
         assert math.isclose(q[k], ref[k], rel_tol=1e-10, abs_tol=1e-300), (k, q[k], ref[k])
 
 
+@pytest.mark.parametrize("ndim,n,order", [(1, 64, 5), (3, 16, 5), (3, 16, 3)])
+@pytest.mark.parametrize("p_left,eps", [(1.0e9, 1e-6), (1.0e10, 1e-40), (2.0e5, 1e6)])
+def test_fp64_smoothness_range(ctx, ndim, n, order, p_left, eps):
+    """Smoothness indicators from far below to far above the epsilon (ratios up
+    to 1e60) against the oracle (the bar of the 100-step runs)."""
+    say("fp64 smoothness range", ndim, order, p_left, eps)
+    cfg = dict(BASE, ndim=ndim, n=n, cloud_radius=0.3, ramp_delta=0.015, ramp_width=0.1, weno_order=order, weno_eps=eps)
+    water = dict(a1r1=1000.0, a2r2=0.0, a2=0.0)
+    W = riemann_primitives(ndim, n, dict(water, p=p_left), dict(water, p=1.0e5))
+    U, _, dts = gpu_run(ctx, cfg, "f64", W=W, n_steps=12)
+    R, rdts = OF.run_steps(cfg, OF.prim_to_cons(cfg, W), 12)
+    np.testing.assert_allclose(dts, rdts, rtol=1e-12, atol=0)
+    err = max_rel_field(oracle_shape(cfg, U), R)
+    assert np.all(err <= 1e-10), err
+
+
 def test_fp64_ragged_tiles_and_chunks(ctx):
     """n = 20 leaves ragged tiles in x, y and z for every tile shape."""
     say("fp64 ragged 20^3")
