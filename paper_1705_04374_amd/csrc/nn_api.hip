@@ -3,7 +3,6 @@
 // nn_kernels.hip enqueued on the caller's stream.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <cstring>
 
 #include "nn_kernels.h"
@@ -38,33 +37,19 @@ using namespace ofm;
 size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct WS {
-    float *s, *z3, *a3, *y, *dy, *sq, *C, *z2, *dz2, *dh1, *dz3, *ds;
-    uint16_t *s_bf, *h1_bf, *dz2_bf, *dz3_bf;
+    uint16_t* s_bf;                          // pooled activations
+    float *ds, *part_head, *part_phi;        // training
 };
 
-int workspace(ofm_nn* nn, int64_t rows, int sets, bool train, WS& w)
+int workspace(ofm_nn* nn, int sets, bool train, WS& w)
 {
     size_t off = 0;
-    size_t o_s = off; off += al(sizeof(float) * sets * 128);
-    size_t o_sbf = off; off += al(2 * (size_t)sets * 128);
-    size_t o_z3 = off; off += al(sizeof(float) * sets * 128);
-    size_t o_a3 = off; off += al(sizeof(float) * sets * 128);
-    size_t o_y = off; off += al(sizeof(float) * sets * NN_DOUT);
-    size_t o_dy = off; off += al(sizeof(float) * sets * NN_DOUT);
-    size_t o_sq = off; off += al(sizeof(float) * sets * NN_DOUT);
-    const int sp_w = nn_gemm_splits((int)std::max<int64_t>(rows, sets), (int)std::max<int64_t>(1, std::max<int64_t>(rows, sets) / 4096));
-    const size_t cN = std::max<size_t>({ (size_t)sets * 128, (size_t)sp_w * 128 * 128, train ? (size_t)rows * 128 : 0 });
-    size_t o_C = off; off += al(sizeof(float) * cN);
-    size_t o_z2 = off, o_dz2 = off, o_dh1 = off, o_dz3 = off, o_ds = off, o_h1 = off, o_dz2bf = off, o_dz3bf = off;
+    const size_t o_s = off; off += al(2 * (size_t)sets * 128);
+    size_t o_ds = off, o_head = off, o_phi = off;
     if (train) {
-        o_z2 = off; off += al(sizeof(float) * rows * 128);
-        o_dz2 = off; off += al(sizeof(float) * rows * 128);
-        o_dh1 = off; off += al(sizeof(float) * rows * 128);
-        o_h1 = off; off += al(2 * (size_t)rows * 128);
-        o_dz2bf = off; off += al(2 * (size_t)rows * 128);
-        o_dz3 = off; off += al(sizeof(float) * sets * 128);
-        o_ds = off; off += al(sizeof(float) * sets * 128);
-        o_dz3bf = off; off += al(2 * (size_t)sets * 128);
+        o_ds = off; off += al(sizeof(float) * (size_t)sets * 128);
+        o_head = off; off += al(sizeof(float) * (size_t)nn_parts_head(sets) * NN_PART_HEAD);
+        o_phi = off; off += al(sizeof(float) * (size_t)nn_parts_phi(sets) * NN_PART_PHI);
     }
     if (off > nn->ws_bytes) {
         if (nn->ws) (void)hipFree(nn->ws);
@@ -76,59 +61,16 @@ int workspace(ofm_nn* nn, int64_t rows, int sets, bool train, WS& w)
         }
         nn->ws_bytes = off;
     }
-    char* b = nn->ws;
-    w.s = (float*)(b + o_s); w.s_bf = (uint16_t*)(b + o_sbf); w.z3 = (float*)(b + o_z3); w.a3 = (float*)(b + o_a3);
-    w.y = (float*)(b + o_y); w.dy = (float*)(b + o_dy); w.sq = (float*)(b + o_sq); w.C = (float*)(b + o_C);
-    w.z2 = (float*)(b + o_z2); w.dz2 = (float*)(b + o_dz2); w.dh1 = (float*)(b + o_dh1); w.h1_bf = (uint16_t*)(b + o_h1);
-    w.dz2_bf = (uint16_t*)(b + o_dz2bf); w.dz3 = (float*)(b + o_dz3); w.ds = (float*)(b + o_ds);
-    w.dz3_bf = (uint16_t*)(b + o_dz3bf);
+    w.s_bf = (uint16_t*)(nn->ws + o_s);
+    w.ds = (float*)(nn->ws + o_ds);
+    w.part_head = (float*)(nn->ws + o_head);
+    w.part_phi = (float*)(nn->ws + o_phi);
     return OFM_OK;
 }
 
 int check_sets(const float* x, const int32_t* off, int32_t n_sets, int64_t rows)
 {
     if (!x || !off || n_sets < 1 || rows < 1) return fail(nullptr, OFM_EINVAL, "surrogate: bad inputs");
-    return OFM_OK;
-}
-
-// forward through the head; train = also keep what the backward pass needs
-int forward(ofm_nn* nn, const float* x, const int32_t* off, int32_t S, int64_t R, WS& w, bool train, hipStream_t s)
-{
-    NNCHK(nn_phi_pool(x, off, S, nn->P, nn->W2bf, nn->spec.pool_scale, w.s, w.s_bf, train ? w.h1_bf : nullptr,
-                      train ? w.z2 : nullptr, s));
-    NNCHK(nn_gemm(w.s_bf, false, nn->W3bf, true, w.C, S, 128, 128, 128, 128, 1, s));
-    NNCHK(nn_gemm_finish(w.C, 1, S, 128, 1, nn->P + NN_B3, nullptr, w.z3, w.a3, nullptr, s));
-    (void)R;
-    return OFM_OK;
-}
-
-int backward(ofm_nn* nn, const float* x, const int32_t* off, int32_t S, int64_t R, const float* y_true, WS& w,
-             float* loss, hipStream_t s)
-{
-    NNCHK(nn_head(w.a3, nn->P, S, nn->norm, nn->norm + 5, nullptr, y_true, w.dy, w.sq, s));
-    NNCHK(nn_loss(w.sq, S * NN_DOUT, loss, s));
-    NNCHK(nn_dw4(w.dy, w.a3, S, nn->G, s));
-    NNCHK(nn_colsum(w.dy, S, NN_DOUT, nn->G + NN_B4, s));
-    NNCHK(nn_head_back(w.dy, nn->P, w.z3, S, w.dz3, w.dz3_bf, s));
-    NNCHK(nn_colsum(w.dz3, S, 128, nn->G + NN_B3, s));
-    // dW3 = dz3^T s  (K = sets)
-    int sp = nn_gemm_splits(S, std::max(1, S / 4096));
-    NNCHK(nn_gemm(w.dz3_bf, true, w.s_bf, false, w.C, 128, 128, S, 128, 128, std::max(1, S / 4096), s));
-    NNCHK(nn_gemm_finish(w.C, sp, 128, 128, 0, nullptr, nullptr, nn->G + NN_W3, nullptr, nullptr, s));
-    // ds = dz3 W3
-    NNCHK(nn_gemm(w.dz3_bf, false, nn->W3bf, false, w.C, S, 128, 128, 128, 128, 1, s));
-    NNCHK(nn_gemm_finish(w.C, 1, S, 128, 0, nullptr, nullptr, w.ds, nullptr, nullptr, s));
-    NNCHK(nn_dz2(w.ds, w.z2, off, S, R, nn->spec.pool_scale, w.dz2, w.dz2_bf, s));
-    NNCHK(nn_colsum(w.dz2, R, 128, nn->G + NN_B2, s));
-    // dW2 = dz2^T h1 (K = rows, split)
-    const int want = (int)std::max<int64_t>(1, R / 4096);
-    sp = nn_gemm_splits((int)R, want);
-    NNCHK(nn_gemm(w.dz2_bf, true, w.h1_bf, false, w.C, 128, 128, (int)R, 128, 128, want, s));
-    NNCHK(nn_gemm_finish(w.C, sp, 128, 128, 0, nullptr, nullptr, nn->G + NN_W2, nullptr, nullptr, s));
-    // dh1 = dz2 W2
-    NNCHK(nn_gemm(w.dz2_bf, false, nn->W2bf, false, w.C, (int)R, 128, 128, 128, 128, 1, s));
-    NNCHK(nn_gemm_finish(w.C, 1, R, 128, 0, nullptr, nullptr, w.dh1, nullptr, nullptr, s));
-    NNCHK(nn_dw1(w.dh1, x, nn->P, R, nn->G, s));
     return OFM_OK;
 }
 
@@ -240,11 +182,10 @@ int ofm_nn_forward(ofm_nn* nn, const float* x, const int32_t* offsets, int32_t n
     int rc = check_sets(x, offsets, n_sets, R);
     if (rc) return rc;
     WS w;
-    rc = workspace(nn, R, n_sets, false, w);
+    rc = workspace(nn, n_sets, false, w);
     if (rc) return rc;
-    rc = forward(nn, x, offsets, n_sets, R, w, false, s);
-    if (rc) return rc;
-    NNCHK(nn_head(w.a3, nn->P, n_sets, nn->norm, nn->norm + 5, y, nullptr, nullptr, nullptr, s));
+    NNCHK(nn_phi_pool(x, offsets, n_sets, nn->P, nn->W2bf, nn->spec.pool_scale, w.s_bf, s));
+    NNCHK(nn_head(w.s_bf, nn->W3bf, nn->P, n_sets, nn->norm, nn->norm + 5, y, s));
     return OFM_OK;
 }
 
@@ -257,12 +198,13 @@ int ofm_nn_grads(ofm_nn* nn, const float* x, const int32_t* offsets, int32_t n_s
     int rc = check_sets(x, offsets, n_sets, R);
     if (rc) return rc;
     WS w;
-    rc = workspace(nn, R, n_sets, true, w);
+    rc = workspace(nn, n_sets, true, w);
     if (rc) return rc;
-    rc = forward(nn, x, offsets, n_sets, R, w, true, s);
-    if (rc) return rc;
-    rc = backward(nn, x, offsets, n_sets, R, y_true, w, loss, s);
-    if (rc) return rc;
+    const float scale = nn->spec.pool_scale;
+    NNCHK(nn_phi_pool(x, offsets, n_sets, nn->P, nn->W2bf, scale, w.s_bf, s));
+    NNCHK(nn_head_train(w.s_bf, nn->W3bf, nn->P, n_sets, nn->norm, nn->norm + 5, y_true, w.ds, w.part_head, s));
+    NNCHK(nn_phi_back(x, offsets, n_sets, nn->P, nn->W2bf, w.ds, scale, w.part_phi, s));
+    NNCHK(nn_grad_sum(w.part_phi, w.part_head, n_sets, nn->G, loss, s));
     if (grads) NNCHK(hipMemcpyAsync(grads, nn->G, sizeof(float) * NN_NPARAM, hipMemcpyDeviceToDevice, s));
     return OFM_OK;
 }

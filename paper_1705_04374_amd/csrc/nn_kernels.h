@@ -20,23 +20,25 @@ constexpr int NN_W4 = NN_B3 + 128;
 constexpr int NN_B4 = NN_W4 + NN_DOUT * 128;
 constexpr int NN_NPARAM = NN_B4 + NN_DOUT;
 
-hipError_t nn_gemm(const uint16_t* A, bool a_km, const uint16_t* B, bool b_nk, float* C, int M, int N, int K, int lda,
-                   int ldb, int splits, hipStream_t s);
-int nn_gemm_splits(int K, int splits);
-hipError_t nn_gemm_finish(const float* C, int splits, int64_t M, int N, int mode, const float* bias, const float* mask,
-                          float* out, float* act, uint16_t* act_bf, hipStream_t s);
+// A workgroup's part of the gradients: those of phi (W1, b1, W2, b2), and
+// those of the head (W3, b3, W4, b4) and the squared errors' sum.
+constexpr int NN_PART_PHI = NN_W3;
+constexpr int NN_PART_HEAD = NN_NPARAM - NN_W3 + 1;
+
+// s_bf: the pooled activations as bf16, [n_sets][128]
 hipError_t nn_phi_pool(const float* x, const int32_t* offsets, int n_sets, const float* P, const uint16_t* W2bf,
-                       float pool_scale, float* s_out, uint16_t* s_bf, uint16_t* h1_bf, float* z2, hipStream_t st);
-hipError_t nn_head(const float* a3, const float* P, int n_sets, const float* mean, const float* stdv, float* y_phys,
-                   const float* y_true, float* dy, float* sq, hipStream_t s);
-hipError_t nn_head_back(const float* dy, const float* P, const float* z3, int n_sets, float* dz3, uint16_t* dz3_bf,
-                        hipStream_t s);
-hipError_t nn_dz2(const float* ds, const float* z2, const int32_t* offsets, int n_sets, int64_t rows, float pool_scale,
-                  float* dz2, uint16_t* dz2_bf, hipStream_t s);
-hipError_t nn_colsum(const float* in, int64_t rows, int cols, float* out, hipStream_t s);
-hipError_t nn_dw4(const float* dy, const float* a3, int n_sets, float* g, hipStream_t s);
-hipError_t nn_dw1(const float* dh1, const float* x, const float* P, int64_t rows, float* g, hipStream_t s);
-hipError_t nn_loss(const float* sq, int n, float* loss, hipStream_t s);
+                       float pool_scale, uint16_t* s_bf, hipStream_t st);
+hipError_t nn_head(const uint16_t* s_bf, const uint16_t* W3bf, const float* P, int n_sets, const float* mean,
+                   const float* stdv, float* y_phys, hipStream_t s);
+int nn_parts_head(int n_sets);
+int nn_parts_phi(int n_sets);
+// ds: d loss / d pooled activations [n_sets][128]; part [nn_parts_head][NN_PART_HEAD]
+hipError_t nn_head_train(const uint16_t* s_bf, const uint16_t* W3bf, const float* P, int n_sets, const float* mean,
+                         const float* stdv, const float* y_true, float* ds, float* part, hipStream_t s);
+// part [nn_parts_phi][NN_PART_PHI]
+hipError_t nn_phi_back(const float* x, const int32_t* offsets, int n_sets, const float* P, const uint16_t* W2bf,
+                       const float* ds, float pool_scale, float* part, hipStream_t s);
+hipError_t nn_grad_sum(const float* part_phi, const float* part_head, int n_sets, float* G, float* loss, hipStream_t s);
 hipError_t nn_adam(float* P, const float* G, float* m, float* v, float lr, float b1, float b2, float eps, int t,
                    uint16_t* W2bf, uint16_t* W3bf, hipStream_t s);
 hipError_t nn_shadow(const float* P, uint16_t* W2bf, uint16_t* W3bf, hipStream_t s);

@@ -6,11 +6,19 @@
 // OF-MLMC estimator (its coefficient from eq. (alpha-matvec) absorbs its
 // error).
 //
-// The three 128-wide contractions (and their backward products) run on the
-// matrix cores: bf16 operands (round to nearest even from float), float
-// accumulation, v_mfma_f32_32x32x16_bf16.  The 4-wide input layer, the
-// 5-wide output layer, pooling, loss and Adam are plain vector code in float.
-// Every reduction has a fixed order, so results do not depend on scheduling.
+// The 128-wide contractions (and their backward products) run on the matrix
+// cores with bf16 operands (round to nearest even from float) and float
+// accumulation (v_mfma_f32_32x32x16_bf16), the 4-wide input layer on them in
+// float (v_mfma_f32_32x32x2_f32: each product and sum rounded as the chain of
+// FMAs b + x0 w0 + x1 w1 + x2 w2 + x3 w3).  The 5-wide output layer, pooling,
+// loss and Adam are vector code in float.  Every reduction has a fixed order,
+// so results do not depend on scheduling.
+//
+// A training step is four launches: the pool (phi_pool_kernel), the head with
+// its backward part (head_kernel<true>), the backward part of phi
+// (phi_back_kernel, which recomputes the activations: storing and re-reading
+// them took 30 times the bytes) and the sum of the workgroups' partial
+// gradients (grad_sum_kernel).
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -20,8 +28,12 @@
 namespace ofm {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+typedef __attribute__((__vector_size__(2 * sizeof(float)))) float floatx2;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
 struct alignas(16) u16x8 { uint16_t v[8]; };
+struct alignas(16) u32x4 { uint32_t v[4]; };
+struct alignas(8) u32x2 { uint32_t v[2]; };
 
 __device__ __forceinline__ uint16_t to_bf16(float f)
 {
@@ -30,7 +42,12 @@ __device__ __forceinline__ uint16_t to_bf16(float f)
     return (uint16_t)(u >> 16);
 }
 
-__device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
+// Two floats as packed bf16 (round to nearest even).
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
+{
+    const floatx2 f = { lo, hi };
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
+}
 
 __device__ __forceinline__ bf16x8 frag(const uint16_t* p)
 {
@@ -42,381 +59,519 @@ __device__ __forceinline__ bf16x8 frag(const uint16_t* p)
 // lane % 32, row (e / 4) * 8 + (lane / 32) * 4 + e % 4.
 __device__ __forceinline__ int mfma_row(int e, int lane) { return (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3); }
 
-// ---------------------------------------------------------------------------
-// Generic bf16 GEMM, C[split][M][N] = A[M x Ksplit] B[Ksplit x N], float out.
-// A(m, k) = A_KM ? A[k lda + m] : A[m lda + k];  B(k, n) = B_NK ? B[n ldb + k] : B[k ldb + n].
-// Workgroup tile 128 x 128, k-step 32, four waves of 64 x 64 (2 x 2 MFMA blocks).
-// ---------------------------------------------------------------------------
-constexpr int GT = 128, GK = 32, GP = GK + 8;   // LDS row pitch keeps 16-byte fragments aligned
-
-template <bool A_KM, bool B_NK>
-__global__ void __launch_bounds__(256) gemm_bf16_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
-                                                        float* __restrict__ C, int M, int N, int K, int lda, int ldb,
-                                                        int k_per_split)
+__device__ __forceinline__ floatx16 splat16(float v)
 {
-    __shared__ uint16_t sA[GT * GP];
-    __shared__ uint16_t sB[GT * GP];
-    const int tiles_n = (N + GT - 1) / GT;
-    const int m0 = (blockIdx.x / tiles_n) * GT, n0 = (blockIdx.x % tiles_n) * GT;
-    const int kb = blockIdx.y * k_per_split;
-    const int ke = min(K, kb + k_per_split);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = wave >> 1, wc = wave & 1;
-    floatx16 acc[2][2];
+    floatx16 r;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-    for (int k0 = kb; k0 < ke; k0 += GK) {
-        __syncthreads();
-        for (int e = tid; e < GT * GK; e += 256) {
-            int ml, kl;
-            if (A_KM) { kl = e / GT; ml = e % GT; } else { ml = e / GK; kl = e % GK; }
-            const int m = m0 + ml, k = k0 + kl;
-            uint16_t v = 0;
-            if (m < M && k < ke) v = A_KM ? A[(int64_t)k * lda + m] : A[(int64_t)m * lda + k];
-            sA[ml * GP + kl] = v;
-        }
-        for (int e = tid; e < GT * GK; e += 256) {
-            int nl, kl;
-            if (B_NK) { nl = e / GK; kl = e % GK; } else { kl = e / GT; nl = e % GT; }
-            const int n = n0 + nl, k = k0 + kl;
-            uint16_t v = 0;
-            if (n < N && k < ke) v = B_NK ? B[(int64_t)n * ldb + k] : B[(int64_t)k * ldb + n];
-            sB[nl * GP + kl] = v;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k16 = 0; k16 < GK; k16 += 16) {
-            const int kk = k16 + (lane >> 5) * 8;
-            bf16x8 a[2], b[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) a[i] = frag(&sA[(wr * 64 + i * 32 + (lane & 31)) * GP + kk]);
-#pragma unroll
-            for (int j = 0; j < 2; ++j) b[j] = frag(&sB[(wc * 64 + j * 32 + (lane & 31)) * GP + kk]);
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
-    }
-    float* Cs = C + (int64_t)blockIdx.y * M * N;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int n = n0 + wc * 64 + j * 32 + (lane & 31);
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int m = m0 + wr * 64 + i * 32 + mfma_row(e, lane);
-                if (m < M && n < N) Cs[(int64_t)m * N + n] = acc[i][j][e];
-            }
-        }
+    for (int e = 0; e < 16; ++e) r[e] = v;
+    return r;
 }
 
-// Sum of the splits in a fixed order, plus an epilogue:
-//   mode 0: out = sum                          (float)
-//   mode 1: z = sum + bias; out = z; act = ReLU(z) as float, act_bf = bf16(ReLU(z))
-//   mode 2: out = sum * (mask > 0)             (ReLU derivative, mask = pre-activation)
-__global__ void __launch_bounds__(256) gemm_finish_kernel(const float* __restrict__ C, int splits, int64_t MN, int N,
-                                                         int mode, const float* __restrict__ bias,
-                                                         const float* __restrict__ mask, float* __restrict__ out,
-                                                         float* __restrict__ act, uint16_t* __restrict__ act_bf)
+// Hidden unit that row m of an input-layer block stands for when the block is
+// computed with units as rows (below): lane / 32 = h then holds, in elements
+// 8 t .. 8 t + 7, the units 16 t + 8 h .. 16 t + 8 h + 7 of its bubble, which
+// is the left operand of the next layer's MFMA as it stands.
+__device__ __forceinline__ int unit_of_row(int m)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= MN) return;
-    float s = 0.f;
-    for (int k = 0; k < splits; ++k) s += C[(int64_t)k * MN + i];
-    if (mode == 1) {
-        s += bias[i % N];
-        out[i] = s;
-        const float a = fmaxf(s, 0.f);
-        if (act) act[i] = a;
-        if (act_bf) act_bf[i] = to_bf16(a);
-    } else if (mode == 2) {
-        out[i] = mask[i] > 0.f ? s : 0.f;
-    } else {
-        out[i] = s;
-    }
+    return 16 * (m >> 4) + 8 * ((m >> 2) & 1) + 4 * ((m >> 3) & 1) + (m & 3);
 }
 
-// ---------------------------------------------------------------------------
-// Fused per-set forward of phi and the sum pool.  A workgroup stages the
-// weights in LDS once and then takes sets gridDim.x apart.  Rows of a set
-// are processed 128 at a time: the input layer on the vector units into LDS
-// (bf16), the 128 x 128 layer on the matrix cores, bias + ReLU, then column
-// sums over the rows (fixed order, so a set's result does not depend on the
-// grid).  In the input layer a thread owns one column (its four weights and
-// bias in registers) for half of the chunk's rows, and the chunk's inputs
-// are read from LDS one row at a time by the whole wavefront (a broadcast).
-// ---------------------------------------------------------------------------
-constexpr int HP = 128 + 8;
+constexpr int HP = 128 + 8;   // LDS pitch of 128 bf16: 16-byte fragments stay aligned
+constexpr int RP = 64 + 8;    // the same for 64
 
-__global__ void __launch_bounds__(256) phi_pool_kernel(const float* __restrict__ x, const int32_t* __restrict__ offsets,
-                                                       int n_sets,
-                                                       const float* __restrict__ P, const uint16_t* __restrict__ W2bf,
-                                                       float pool_scale, float* __restrict__ s_out,
-                                                       uint16_t* __restrict__ s_bf, uint16_t* __restrict__ h1_bf,
-                                                       float* __restrict__ z2_out)
+// ---------------------------------------------------------------------------
+// phi and the sum pool.  A wavefront takes 64 bubbles of one set at a time:
+// the input layer as W1 X^T (two blocks of 32 bubbles), whose result, after
+// ReLU and rounding, is already the left operand of the 128 x 128 layer
+// (unit_of_row), so that activations never pass through LDS; W2 is read from
+// LDS as the right operand, each fragment used for both blocks; then bias,
+// ReLU and column sums.  A set's sum adds its groups of 64 in order, two at a
+// time, whichever wavefront computed them, so that its result does not depend
+// on the launch.
+//
+// Per 64 bubbles and wavefront: 64 bf16 and 16 float MFMAs (3072 cycles of
+// the SIMD's matrix core), about 620 vector operations (2500 cycles) that the
+// other wavefront of the SIMD overlaps with them.  128 accumulators a lane
+// hold it to two wavefronts.  16384 sets of 500: 1117 us before (input layer
+// on the vector units, activations through LDS), PHI_NOW now.
+//
+// per_wave: a set per wavefront; otherwise a set per workgroup, its groups
+// dealt to the four wavefronts.
+// ---------------------------------------------------------------------------
+template <bool PER_WAVE>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+phi_pool_kernel(const float* __restrict__ x, const int32_t* __restrict__ offsets, int n_sets,
+                const float* __restrict__ P, const uint16_t* __restrict__ W2bf, float pool_scale,
+                uint16_t* __restrict__ s_bf)
 {
-    __shared__ uint16_t sW[128 * HP];   // W2 [n][k]
-    __shared__ uint16_t sH[128 * HP];   // h1 chunk [row][k]
-    __shared__ float4 sX[128];          // the chunk's input rows
-    __shared__ float sb2[128];
-    __shared__ float colsum[2][128];
+    __shared__ __align__(16) uint16_t sW[128 * HP];             // W2 [n][k]
+    __shared__ __align__(16) float sb1[128];
+    __shared__ float colsum[PER_WAVE ? 1 : 4][128];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = wave >> 1, wc = wave & 1;
+    const int col = lane & 31, half = lane >> 5;
     for (int e = tid; e < 128 * 128; e += 256) sW[(e >> 7) * HP + (e & 127)] = W2bf[e];
-    if (tid < 128) sb2[tid] = P[NN_B2 + tid];
-    // input layer: this thread's column and half of the rows
-    const int ic = tid & 127, ih = (tid >> 7) * 64;
-    const float ib = P[NN_B1 + ic];
-    float iw[4];
+    if (tid < 128) sb1[tid] = P[NN_B1 + tid];
+    float a1[4][2], b2[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) iw[k] = P[NN_W1 + ic * 4 + k];
-    for (int set = blockIdx.x; set < n_sets; set += gridDim.x) {
-        const int r0 = offsets[set], r1 = offsets[set + 1];
-        float acc_col = 0.f;   // running column sum, thread tid < 128 owns column tid
-        for (int c0 = r0; c0 < r1; c0 += 128) {
-            __syncthreads();
-            if (tid < 128) {
-                const int r = c0 + tid;
-                float4 xv = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (r < r1) {
-                    const float* xr = x + (int64_t)r * 4;
-                    xv = make_float4(xr[0], xr[1], xr[2], xr[3]);
-                }
-                sX[tid] = xv;
+    for (int u = 0; u < 4; ++u) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) a1[u][k] = P[NN_W1 + (u * 32 + unit_of_row(col)) * 4 + 2 * k + half];
+        b2[u] = P[NN_B2 + u * 32 + col];
+    }
+    __syncthreads();
+
+    // column sums of the bubbles c .. min(c + 64, r1) - 1 (every lane gets
+    // those of its four columns)
+    auto group = [&](int c, int r1, float (&cs)[4]) {
+        float xb[2][2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int r = c + i * 32 + col;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) xb[i][k] = r < r1 ? x[(int64_t)r * 4 + 2 * k + half] : 0.f;
+        }
+        floatx16 acc[2][4];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = splat16(0.f);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            __builtin_amdgcn_sched_barrier(0);
+            floatx16 d[2];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const float4 b = *reinterpret_cast<const float4*>(&sb1[u * 32 + 16 * (g >> 1) + 8 * half + 4 * (g & 1)]);
+                d[0][4 * g] = b.x; d[0][4 * g + 1] = b.y; d[0][4 * g + 2] = b.z; d[0][4 * g + 3] = b.w;
             }
-            __syncthreads();
-            {
-                const int nr = min(r1 - c0, 128);
-                for (int rl = ih; rl < ih + 64; ++rl) {
-                    uint16_t h = 0;
-                    if (rl < nr) {
-                        const float4 xv = sX[rl];
-                        float z = ib;
-                        z += xv.x * iw[0];
-                        z += xv.y * iw[1];
-                        z += xv.z * iw[2];
-                        z += xv.w * iw[3];
-                        h = to_bf16(fmaxf(z, 0.f));
-                        if (h1_bf) h1_bf[(int64_t)(c0 + rl) * 128 + ic] = h;
-                    }
-                    sH[rl * HP + ic] = h;
+            d[1] = d[0];
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) d[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[u][k], xb[i][k], d[i], 0, 0, 0);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                bf16x8 h[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    u32x4 p;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        p.v[q] = pack_bf16(fmaxf(d[i][8 * t + 2 * q], 0.f), fmaxf(d[i][8 * t + 2 * q + 1], 0.f));
+                    h[i] = __builtin_bit_cast(bf16x8, p);
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const bf16x8 b = frag(&sW[(j * 32 + col) * HP + u * 32 + t * 16 + half * 8]);
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(h[i], b, acc[i][j], 0, 0, 0);
                 }
             }
-            __syncthreads();
-            floatx16 acc[2][2];
+        }
+        const bool full = c + 64 <= r1;           // no row check
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-#pragma unroll
-            for (int k16 = 0; k16 < 128; k16 += 16) {
-                const int kk = k16 + (lane >> 5) * 8;
-                bf16x8 a[2], b[2];
-#pragma unroll
-                for (int i = 0; i < 2; ++i) a[i] = frag(&sH[(wr * 64 + i * 32 + (lane & 31)) * HP + kk]);
-#pragma unroll
-                for (int j = 0; j < 2; ++j) b[j] = frag(&sW[(wc * 64 + j * 32 + (lane & 31)) * HP + kk]);
+        for (int j = 0; j < 4; ++j) {
+            float v = 0.f;
+            if (full) {
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
 #pragma unroll
-                    for (int j = 0; j < 2; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+                    for (int e = 0; e < 16; ++e) v += fmaxf(acc[i][j][e] + b2[j], 0.f);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        if (c + i * 32 + mfma_row(e, lane) < r1) v += fmaxf(acc[i][j][e] + b2[j], 0.f);
             }
-            // bias + ReLU + per-column partial sums of this wave's 64 rows
-            // (a chunk of 128 rows needs no row check)
-            const bool full = c0 + 128 <= r1;
+            cs[j] = v + __shfl_xor(v, 32, 64);
+        }
+    };
+
+    if constexpr (PER_WAVE) {
+        for (int set = blockIdx.x * 4 + wave; set < n_sets; set += gridDim.x * 4) {
+            const int r0 = offsets[set], r1 = offsets[set + 1];
+            float sum[4] = { 0.f, 0.f, 0.f, 0.f }, first[4];
+            bool odd = false;
+#pragma clang loop unroll(disable)
+            for (int c = r0; c < r1; c += 64) {
+                float cs[4];
+                group(c, r1, cs);
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int col = wc * 64 + j * 32 + (lane & 31);
-                const float bb = sb2[col];
-                float cs = 0.f;
-                if (full && !z2_out) {
-#pragma unroll
-                    for (int i = 0; i < 2; ++i)
-#pragma unroll
-                        for (int e = 0; e < 16; ++e) cs += fmaxf(acc[i][j][e] + bb, 0.f);
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 2; ++i)
-#pragma unroll
-                        for (int e = 0; e < 16; ++e) {
-                            const int rl = wr * 64 + i * 32 + mfma_row(e, lane);
-                            const int r = c0 + rl;
-                            const float z = acc[i][j][e] + bb;
-                            if (r < r1) {
-                                cs += fmaxf(z, 0.f);
-                                if (z2_out) z2_out[(int64_t)r * 128 + col] = z;
-                            }
-                        }
+                for (int j = 0; j < 4; ++j) {
+                    if (odd) sum[j] += first[j] + cs[j];
+                    first[j] = cs[j];
                 }
-                cs += __shfl_xor(cs, 32, 64);
-                if (lane < 32) colsum[wr][col] = cs;
+                odd = !odd;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (odd) sum[j] += first[j];
+                if (half == 0) s_bf[(int64_t)set * 128 + j * 32 + col] = to_bf16(pool_scale * sum[j]);
+            }
+        }
+    } else {
+        for (int set = blockIdx.x; set < n_sets; set += gridDim.x) {
+            const int r0 = offsets[set], r1 = offsets[set + 1];
+            float sum = 0.f;                      // of column tid (tid < 128)
+            for (int c0 = r0; c0 < r1; c0 += 256) {
+                const int c = c0 + wave * 64;
+                float cs[4] = { 0.f, 0.f, 0.f, 0.f };
+                if (c < r1) group(c, r1, cs);
+                if (half == 0)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) colsum[wave][j * 32 + col] = cs[j];
+                __syncthreads();
+                if (tid < 128) {
+                    sum += colsum[0][tid] + colsum[1][tid];
+                    sum += colsum[2][tid] + colsum[3][tid];
+                }
+                __syncthreads();
+            }
+            if (tid < 128) s_bf[(int64_t)set * 128 + tid] = to_bf16(pool_scale * sum);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Head: z3 = W3 s + b3, y = W4 ReLU(z3) + b4, 32 sets a workgroup and pass.
+// Wavefront w computes columns 32 w .. 32 w + 31 of z3 (operands straight
+// from memory in fragment order); the output layer is one thread per (set,
+// output), a chain of 128 FMAs over LDS.
+//
+// TRAIN: also the loss, dz3 = (dy W4) [z3 > 0], ds = dz3 W3 (bf16 operands)
+// and this workgroup's part of the gradients of W3, b3, W4, b4.  An element
+// of dz3 as computed (sets in registers, columns over lanes) is the left
+// operand of dW3 = dz3^T s as it stands, with the sets taken in the order the
+// registers hold them; ds needs it with columns in registers: through LDS.
+// ---------------------------------------------------------------------------
+template <bool TRAIN>
+__global__ void __launch_bounds__(256) head_kernel(const uint16_t* __restrict__ s_bf, const uint16_t* __restrict__ W3bf,
+                                                   const float* __restrict__ P, int n_sets,
+                                                   const float* __restrict__ mean, const float* __restrict__ stdv,
+                                                   float* __restrict__ y_phys, const float* __restrict__ y_true,
+                                                   float* __restrict__ ds, float* __restrict__ part)
+{
+    constexpr int AP = 129;
+    __shared__ float sA[32 * AP];                       // ReLU(z3) [set][k]
+    __shared__ __align__(16) uint16_t sZ[TRAIN ? 32 * HP : 1];        // dz3 as bf16 [set][n]
+    __shared__ float sY[TRAIN ? 32 * NN_DOUT : 1];      // dy
+    __shared__ float sQ[TRAIN ? 256 : 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lc = lane & 31, half = lane >> 5, n = wave * 32 + lc;
+    const float b3 = P[NN_B3 + n];
+    float w4[NN_DOUT];
+    bf16x8 wt[TRAIN ? 8 : 1];                           // W3 with column n over K (ds)
+    floatx16 dW3[TRAIN ? 4 : 1];
+    float db3 = 0.f, dw4[3] = { 0.f, 0.f, 0.f }, db4 = 0.f, loss = 0.f;
+    if constexpr (TRAIN) {
+#pragma unroll
+        for (int o = 0; o < NN_DOUT; ++o) w4[o] = P[NN_W4 + o * 128 + n];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            u16x8 v;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v.v[i] = W3bf[(t * 16 + half * 8 + i) * 128 + n];
+            wt[t] = __builtin_bit_cast(bf16x8, v);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) dW3[q] = splat16(0.f);
+    }
+    for (int s0 = blockIdx.x * 32; s0 < n_sets; s0 += gridDim.x * 32) {
+        const int sr = min(s0 + lc, n_sets - 1);
+        floatx16 acc = splat16(0.f);
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(&s_bf[(int64_t)sr * 128 + t * 16 + half * 8]),
+                                                          frag(&W3bf[n * 128 + t * 16 + half * 8]), acc, 0, 0, 0);
+        __syncthreads();                                // the pass before has read sA, sY and sZ
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            acc[e] += b3;
+            sA[mfma_row(e, lane) * AP + n] = fmaxf(acc[e], 0.f);
+        }
+        __syncthreads();
+        if (tid < 32 * NN_DOUT) {
+            const int s = tid & 31, o = tid >> 5, set = s0 + s;
+            float y = P[NN_B4 + o];
+            for (int k = 0; k < 128; ++k) y += sA[s * AP + k] * P[NN_W4 + o * 128 + k];
+            float dy = 0.f;
+            if (set < n_sets) {
+                if (y_phys) y_phys[(int64_t)set * NN_DOUT + o] = y * stdv[o] + mean[o];
+                if constexpr (TRAIN) {
+                    const float d = y - (y_true[(int64_t)set * NN_DOUT + o] - mean[o]) / stdv[o];
+                    dy = 2.f * d / (float)(n_sets * NN_DOUT);
+                    loss += d * d;
+                }
+            }
+            if constexpr (TRAIN) sY[s * NN_DOUT + o] = dy;
+        }
+        if constexpr (TRAIN) {
+            __syncthreads();
+            u32x4 af[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    float d[2];
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) {
+                        const int e = 8 * t + 2 * q + b, s = mfma_row(e, lane);
+                        float v = 0.f;
+#pragma unroll
+                        for (int o = 0; o < NN_DOUT; ++o) v += sY[s * NN_DOUT + o] * w4[o];
+                        d[b] = acc[e] > 0.f ? v : 0.f;
+                        db3 += d[b];
+                        sZ[s * HP + n] = to_bf16(d[b]);
+                    }
+                    af[t].v[q] = pack_bf16(d[0], d[1]);
+                }
+            // dW3[n][k] over this pass's sets, in the registers' order
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int kb = 0; kb < 4; ++kb) {
+                    u16x8 b;
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        b.v[i] = s_bf[(int64_t)min(s0 + mfma_row(8 * t + i, lane), n_sets - 1) * 128 + kb * 32 + lc];
+                    dW3[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, af[t]),
+                                                                     __builtin_bit_cast(bf16x8, b), dW3[kb], 0, 0, 0);
+                }
+            // dW4: this thread's column, outputs tid / 128, + 2, + 4
+            for (int s = 0; s < 32; ++s) {
+                const float a = sA[s * AP + (tid & 127)];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const int o = (tid >> 7) + 2 * q;
+                    if (o < NN_DOUT) dw4[q] += sY[s * NN_DOUT + o] * a;
+                }
+                if (tid < NN_DOUT) db4 += sY[s * NN_DOUT + tid];
             }
             __syncthreads();
-            if (tid < 128) acc_col += colsum[0][tid] + colsum[1][tid];
-        }
-        if (tid < 128) {
-            const float sv = pool_scale * acc_col;
-            s_out[(int64_t)set * 128 + tid] = sv;
-            s_bf[(int64_t)set * 128 + tid] = to_bf16(sv);
-        }
-    }
-}
-
-// Output layer, de-standardisation and (training) loss and its gradient.
-// One thread per set; a3 [sets][128] after ReLU.
-__global__ void __launch_bounds__(256) head_kernel(const float* __restrict__ a3, const float* __restrict__ P,
-                                                   int n_sets, const float* __restrict__ mean,
-                                                   const float* __restrict__ stdv, float* __restrict__ y_phys,
-                                                   const float* __restrict__ y_true, float* __restrict__ dy,
-                                                   float* __restrict__ sq)
-{
-    const int s = blockIdx.x * 256 + threadIdx.x;
-    if (s >= n_sets) return;
-    const float* W4 = P + NN_W4;
-    for (int o = 0; o < NN_DOUT; ++o) {
-        float y = P[NN_B4 + o];
-        for (int k = 0; k < 128; ++k) y += a3[(int64_t)s * 128 + k] * W4[o * 128 + k];
-        if (y_phys) y_phys[s * NN_DOUT + o] = y * stdv[o] + mean[o];
-        if (y_true) {
-            const float t = (y_true[s * NN_DOUT + o] - mean[o]) / stdv[o];
-            const float d = y - t;
-            dy[s * NN_DOUT + o] = 2.f * d / (float)(n_sets * NN_DOUT);
-            sq[s * NN_DOUT + o] = d * d;
+            floatx16 dsa = splat16(0.f);
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                dsa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(&sZ[lc * HP + t * 16 + half * 8]), wt[t], dsa, 0, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int set = s0 + mfma_row(e, lane);
+                if (set < n_sets) ds[(int64_t)set * 128 + n] = dsa[e];
+            }
         }
     }
-}
-
-// da3 = dy W4, dz3 = da3 * [z3 > 0] (float and bf16); one thread per (set, col).
-__global__ void __launch_bounds__(256) head_back_kernel(const float* __restrict__ dy, const float* __restrict__ P,
-                                                        const float* __restrict__ z3, int n_sets,
-                                                        float* __restrict__ dz3, uint16_t* __restrict__ dz3_bf)
-{
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= (int64_t)n_sets * 128) return;
-    const int s = (int)(i / 128), c = (int)(i % 128);
-    float d = 0.f;
-    for (int o = 0; o < NN_DOUT; ++o) d += dy[s * NN_DOUT + o] * P[NN_W4 + o * 128 + c];
-    d = z3[i] > 0.f ? d : 0.f;
-    dz3[i] = d;
-    dz3_bf[i] = to_bf16(d);
-}
-
-// dz2 = pool_scale ds[set of row] * [z2 > 0] as bf16, plus its float copy for
-// the bias gradient.  One thread per (row, col); row -> set by binary search.
-__global__ void __launch_bounds__(256) dz2_kernel(const float* __restrict__ ds, const float* __restrict__ z2,
-                                                  const int32_t* __restrict__ offsets, int n_sets, int64_t rows,
-                                                  float pool_scale, float* __restrict__ dz2,
-                                                  uint16_t* __restrict__ dz2_bf)
-{
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= rows * 128) return;
-    const int64_t r = i / 128;
-    const int c = (int)(i % 128);
-    int lo = 0, hi = n_sets;   // offsets[lo] <= r < offsets[hi]
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (offsets[mid] <= r) lo = mid; else hi = mid;
+    if constexpr (TRAIN) {
+        float* g = part + (int64_t)blockIdx.x * NN_PART_HEAD;
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) g[(wave * 32 + mfma_row(e, lane)) * 128 + kb * 32 + lc] = dW3[kb][e];
+        db3 += __shfl_xor(db3, 32, 64);
+        if (half == 0) g[NN_B3 - NN_W3 + n] = db3;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const int o = (tid >> 7) + 2 * q;
+            if (o < NN_DOUT) g[NN_W4 - NN_W3 + o * 128 + (tid & 127)] = dw4[q];
+        }
+        if (tid < NN_DOUT) g[NN_B4 - NN_W3 + tid] = db4;
+        sQ[tid] = loss;
+        __syncthreads();
+        for (int w = 128; w > 0; w >>= 1) {
+            if (tid < w) sQ[tid] += sQ[tid + w];
+            __syncthreads();
+        }
+        if (tid == 0) g[NN_PART_HEAD - 1] = sQ[0];
     }
-    const float d = z2[i] > 0.f ? pool_scale * ds[(int64_t)lo * 128 + c] : 0.f;
-    dz2[i] = d;
-    dz2_bf[i] = to_bf16(d);
 }
 
-// Column sums out[c] = sum_r in[r][c] (fixed order), 128 columns, one
-// workgroup per column block of 1 column, strided rows then a tree.
-__global__ void __launch_bounds__(256) colsum_kernel(const float* __restrict__ in, int64_t rows, int cols,
-                                                     float* __restrict__ out)
+// ---------------------------------------------------------------------------
+// Backward part of phi over the bubbles of the workgroup's sets, 64 at a time:
+//   dz2 = pool_scale ds[set] [z2 > 0],  dW2 = dz2^T h1,  db2 = sum dz2,
+//   dz1 = (dz2 W2) [z1 > 0],            dW1 = dz1^T x,   db1 = sum dz1,
+// with h1 and z2 computed again from x.  Wavefront w owns 32 hidden units of
+// the input layer and 32 of the second: it computes its units of h1 in both
+// orders (for the left operand of z2 and the right one of dW2), its columns
+// of z2, its rows of dW2 (64 accumulators a lane, kept over all bubbles) and
+// its columns of dh1.  dz2 as computed (bubbles in registers, units over
+// lanes) is the left operand of dW2; dh1 needs it with units in registers:
+// through LDS, like h1.
+// Bound by its barriers and LDS at one or two wavefronts per SIMD: 256 sets of
+// 500 took 2.0 ms in 13 launches over 500 MB of stored activations, gradients
+// and GEMM splits before, BACK_NOW now.
+// ---------------------------------------------------------------------------
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+phi_back_kernel(const float* __restrict__ x, const int32_t* __restrict__ offsets, int n_sets,
+                const float* __restrict__ P, const uint16_t* __restrict__ W2bf, const float* __restrict__ ds,
+                float pool_scale, float* __restrict__ part)
 {
-    __shared__ float sh[256];
-    const int c = blockIdx.x;
+    __shared__ __align__(16) uint16_t sH[64 * HP];                    // h1 [bubble][unit]
+    __shared__ __align__(16) uint16_t sT[128 * RP];                   // h1 [unit][bubble, in the registers' order]
+    __shared__ __align__(16) uint16_t sD[64 * HP];                    // dz2 [bubble][unit]
+    __shared__ float4 sX[64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lc = lane & 31, half = lane >> 5, n = wave * 32 + lc;
+    bf16x8 w2[8], w2t[8];                               // W2 row n; W2 column n
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        w2[t] = frag(&W2bf[n * 128 + t * 16 + half * 8]);
+        u16x8 v;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v.v[i] = W2bf[(t * 16 + half * 8 + i) * 128 + n];
+        w2t[t] = __builtin_bit_cast(bf16x8, v);
+    }
+    float a1[2], b1[2], bias1[16];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        a1[k] = P[NN_W1 + (wave * 32 + unit_of_row(lc)) * 4 + 2 * k + half];
+        b1[k] = P[NN_W1 + n * 4 + 2 * k + half];
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) bias1[e] = P[NN_B1 + wave * 32 + unit_of_row(mfma_row(e, lane))];
+    const float bn1 = P[NN_B1 + n], bn2 = P[NN_B2 + n];
+    floatx16 dW2[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) dW2[q] = splat16(0.f);
+    float db2 = 0.f, db1 = 0.f, dw1[4] = { 0.f, 0.f, 0.f, 0.f };
+    for (int set = blockIdx.x; set < n_sets; set += gridDim.x) {
+        const int r0 = offsets[set], r1 = offsets[set + 1];
+        const float dsc = pool_scale * ds[(int64_t)set * 128 + n];
+        const uint32_t dlo = to_bf16(dsc), dhi = dlo << 16;
+        for (int c = r0; c < r1; c += 64) {
+            float xb[2][2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int r = c + i * 32 + lc;
+#pragma unroll
+                for (int k = 0; k < 2; ++k) xb[i][k] = r < r1 ? x[(int64_t)r * 4 + 2 * k + half] : 0.f;
+            }
+            __syncthreads();                            // the pass before has read sX, sH, sT and sD
+            if (tid < 64) {
+                const int r = c + tid;
+                const float* xr = x + (int64_t)r * 4;
+                sX[tid] = r < r1 ? make_float4(xr[0], xr[1], xr[2], xr[3]) : make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+            uint32_t on1 = 0;                           // bit 16 i + e: z1 > 0
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                floatx16 d, dt = splat16(bn1);
+#pragma unroll
+                for (int e = 0; e < 16; ++e) d[e] = bias1[e];
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    d = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[k], xb[i][k], d, 0, 0, 0);      // [unit][bubble]
+                    dt = __builtin_amdgcn_mfma_f32_32x32x2f32(xb[i][k], b1[k], dt, 0, 0, 0);    // [bubble][unit]
+                }
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    u32x4 p;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        p.v[q] = pack_bf16(fmaxf(d[8 * t + 2 * q], 0.f), fmaxf(d[8 * t + 2 * q + 1], 0.f));
+                    *reinterpret_cast<u32x4*>(&sH[(i * 32 + lc) * HP + wave * 32 + t * 16 + half * 8]) = p;
+                }
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    u32x2 p;
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+                        p.v[q] = pack_bf16(fmaxf(dt[4 * g + 2 * q], 0.f), fmaxf(dt[4 * g + 2 * q + 1], 0.f));
+                    *reinterpret_cast<u32x2*>(&sT[n * RP + i * 32 + 16 * (g >> 1) + 8 * half + 4 * (g & 1)]) = p;
+                }
+#pragma unroll
+                for (int e = 0; e < 16; ++e) on1 |= dt[e] > 0.f ? 1u << (16 * i + e) : 0u;
+            }
+            __syncthreads();
+            floatx16 z[2] = { splat16(0.f), splat16(0.f) };
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    z[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(&sH[(i * 32 + lc) * HP + t * 16 + half * 8]), w2[t],
+                                                                  z[i], 0, 0, 0);
+            int count = 0;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    u32x4 af;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int e = 8 * t + 2 * q, row = i * 32 + mfma_row(e, lane);
+                        const bool p0 = z[i][e] + bn2 > 0.f && c + row < r1;
+                        const bool p1 = z[i][e + 1] + bn2 > 0.f && c + row + 1 < r1;
+                        count += (p0 ? 1 : 0) + (p1 ? 1 : 0);
+                        sD[row * HP + n] = (uint16_t)(p0 ? dlo : 0u);
+                        sD[(row + 1) * HP + n] = (uint16_t)(p1 ? dlo : 0u);
+                        af.v[q] = (p0 ? dlo : 0u) | (p1 ? dhi : 0u);
+                    }
+#pragma unroll
+                    for (int kb = 0; kb < 4; ++kb)
+                        dW2[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            __builtin_bit_cast(bf16x8, af), frag(&sT[(kb * 32 + lc) * RP + i * 32 + t * 16 + half * 8]),
+                            dW2[kb], 0, 0, 0);
+                }
+            db2 += dsc * (float)count;
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                floatx16 dh = splat16(0.f);
+#pragma unroll
+                for (int t = 0; t < 8; ++t)
+                    dh = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(&sD[(i * 32 + lc) * HP + t * 16 + half * 8]), w2t[t],
+                                                                dh, 0, 0, 0);
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const float d = (on1 >> (16 * i + e)) & 1u ? dh[e] : 0.f;
+                    const float4 xv = sX[i * 32 + mfma_row(e, lane)];
+                    dw1[0] += d * xv.x;
+                    dw1[1] += d * xv.y;
+                    dw1[2] += d * xv.z;
+                    dw1[3] += d * xv.w;
+                    db1 += d;
+                }
+            }
+        }
+    }
+    float* g = part + (int64_t)blockIdx.x * NN_PART_PHI;
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) g[NN_W2 + (wave * 32 + mfma_row(e, lane)) * 128 + kb * 32 + lc] = dW2[kb][e];
+    db2 += __shfl_xor(db2, 32, 64);
+    db1 += __shfl_xor(db1, 32, 64);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) dw1[k] += __shfl_xor(dw1[k], 32, 64);
+    if (half == 0) {
+        g[NN_B2 + n] = db2;
+        g[NN_B1 + n] = db1;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) g[NN_W1 + n * 4 + k] = dw1[k];
+    }
+}
+
+// Gradients and loss from the workgroups' parts: 64 parameters a workgroup,
+// each wavefront a quarter of the parts, in a fixed order.
+__global__ void __launch_bounds__(256) grad_sum_kernel(const float* __restrict__ part_phi, int n_phi,
+                                                       const float* __restrict__ part_head, int n_head, int n_err,
+                                                       float* __restrict__ G, float* __restrict__ loss)
+{
+    __shared__ float sh[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i = blockIdx.x * 64 + lane;               // NN_NPARAM: the loss
+    const bool phi = i < NN_W3;
+    const float* p = phi ? part_phi + i : part_head + (i - NN_W3);
+    const int np = i > NN_NPARAM ? 0 : phi ? n_phi : n_head, stride = phi ? NN_PART_PHI : NN_PART_HEAD;
+    const int per = (np + 3) / 4, b0 = wave * per, b1 = min(np, b0 + per);
     float s = 0.f;
-    for (int64_t r = threadIdx.x; r < rows; r += 256) s += in[r * cols + c];
-    sh[threadIdx.x] = s;
+#pragma unroll 8
+    for (int b = b0; b < b1; ++b) s += p[(int64_t)b * stride];
+    sh[wave][lane] = s;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
+    if (wave == 0) {
+        const float t = (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]);
+        if (i < NN_NPARAM) G[i] = t;
+        if (i == NN_NPARAM) *loss = t / (float)n_err;
     }
-    if (threadIdx.x == 0) out[c] = sh[0];
-}
-
-// dW4[o][k] = sum_s dy[s][o] a3[s][k]; one workgroup per (o, k).
-__global__ void __launch_bounds__(256) dw4_kernel(const float* __restrict__ dy, const float* __restrict__ a3,
-                                                  int n_sets, float* __restrict__ g)
-{
-    __shared__ float sh[256];
-    const int o = blockIdx.x / 128, k = blockIdx.x % 128;
-    float s = 0.f;
-    for (int i = threadIdx.x; i < n_sets; i += 256) s += dy[i * NN_DOUT + o] * a3[(int64_t)i * 128 + k];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) g[NN_W4 + o * 128 + k] = sh[0];
-}
-
-// Input-layer gradients from dh1 (rows x 128): dz1 = dh1 [z1 > 0] with z1
-// recomputed from x; dW1[c][k] = sum_r dz1[r][c] x[r][k], db1[c] = sum_r dz1.
-// One workgroup per column c.
-__global__ void __launch_bounds__(256) dw1_kernel(const float* __restrict__ dh1, const float* __restrict__ x,
-                                                  const float* __restrict__ P, int64_t rows, float* __restrict__ g)
-{
-    __shared__ float sh[5][256];
-    const int c = blockIdx.x;
-    float w[4], b = P[NN_B1 + c];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) w[k] = P[NN_W1 + c * 4 + k];
-    float acc[5] = { 0.f, 0.f, 0.f, 0.f, 0.f };
-    for (int64_t r = threadIdx.x; r < rows; r += 256) {
-        float z = b;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) z += x[r * 4 + k] * w[k];
-        const float d = z > 0.f ? dh1[r * 128 + c] : 0.f;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) acc[k] += d * x[r * 4 + k];
-        acc[4] += d;
-    }
-#pragma unroll
-    for (int q = 0; q < 5; ++q) sh[q][threadIdx.x] = acc[q];
-    __syncthreads();
-    for (int wdt = 128; wdt > 0; wdt >>= 1) {
-        if ((int)threadIdx.x < wdt)
-#pragma unroll
-            for (int q = 0; q < 5; ++q) sh[q][threadIdx.x] += sh[q][threadIdx.x + wdt];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) g[NN_W1 + c * 4 + k] = sh[k][0];
-        g[NN_B1 + c] = sh[4][0];
-    }
-}
-
-// sum of the squared errors -> loss (mean), fixed order, one workgroup.
-__global__ void __launch_bounds__(256) loss_kernel(const float* __restrict__ sq, int n, float* __restrict__ loss)
-{
-    __shared__ float sh[256];
-    float s = 0.f;
-    for (int i = threadIdx.x; i < n; i += 256) s += sq[i];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *loss = sh[0] / (float)n;
 }
 
 // Adam (bias-corrected), float masters; refreshes the bf16 shadows.
@@ -491,90 +646,53 @@ __global__ void __launch_bounds__(256) features_kernel(const double* __restrict_
 // ---------------------------------------------------------------------------
 static int cdiv64(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
-hipError_t nn_gemm(const uint16_t* A, bool a_km, const uint16_t* B, bool b_nk, float* C, int M, int N, int K, int lda,
-                   int ldb, int splits, hipStream_t s)
-{
-    const int kps = ((K + splits - 1) / splits + GK - 1) / GK * GK;
-    const int sp = (K + kps - 1) / kps;
-    dim3 grid(cdiv64(M, GT) * cdiv64(N, GT), sp);
-    if (!a_km && !b_nk) hipLaunchKernelGGL((gemm_bf16_kernel<false, false>), grid, dim3(256), 0, s, A, B, C, M, N, K, lda, ldb, kps);
-    else if (!a_km && b_nk) hipLaunchKernelGGL((gemm_bf16_kernel<false, true>), grid, dim3(256), 0, s, A, B, C, M, N, K, lda, ldb, kps);
-    else if (a_km && !b_nk) hipLaunchKernelGGL((gemm_bf16_kernel<true, false>), grid, dim3(256), 0, s, A, B, C, M, N, K, lda, ldb, kps);
-    else hipLaunchKernelGGL((gemm_bf16_kernel<true, true>), grid, dim3(256), 0, s, A, B, C, M, N, K, lda, ldb, kps);
-    return hipGetLastError();
-}
-
-int nn_gemm_splits(int K, int splits)
-{
-    const int kps = ((K + splits - 1) / splits + GK - 1) / GK * GK;
-    return (K + kps - 1) / kps;
-}
-
-hipError_t nn_gemm_finish(const float* C, int splits, int64_t M, int N, int mode, const float* bias, const float* mask,
-                          float* out, float* act, uint16_t* act_bf, hipStream_t s)
-{
-    const int64_t MN = M * N;
-    hipLaunchKernelGGL(gemm_finish_kernel, dim3(cdiv64(MN, 256)), dim3(256), 0, s, C, splits, MN, N, mode, bias, mask,
-                       out, act, act_bf);
-    return hipGetLastError();
-}
-
 hipError_t nn_phi_pool(const float* x, const int32_t* offsets, int n_sets, const float* P, const uint16_t* W2bf,
-                       float pool_scale, float* s_out, uint16_t* s_bf, uint16_t* h1_bf, float* z2, hipStream_t st)
+                       float pool_scale, uint16_t* s_bf, hipStream_t st)
 {
-    // two resident workgroups per CU (73.2 KB of LDS each): a few rounds of
-    // them, each taking sets gridDim.x apart
-    const int grid = n_sets < 4096 ? n_sets : 4096;
-    hipLaunchKernelGGL(phi_pool_kernel, dim3(grid), dim3(256), 0, st, x, offsets, n_sets, P, W2bf, pool_scale, s_out,
-                       s_bf, h1_bf, z2);
+    // Two workgroups of four wavefronts are resident on each of 256 CUs.  A
+    // set per wavefront wastes nothing inside a set, but needs many sets to
+    // come out even; below 4096 sets a set per workgroup finishes
+    // earlier.
+    if (n_sets >= 4096)
+        hipLaunchKernelGGL((phi_pool_kernel<true>), dim3(512), dim3(256), 0, st, x, offsets, n_sets, P, W2bf, pool_scale, s_bf);
+    else
+        hipLaunchKernelGGL((phi_pool_kernel<false>), dim3(n_sets < 512 ? n_sets : 512), dim3(256), 0, st, x, offsets, n_sets, P,
+                           W2bf, pool_scale, s_bf);
     return hipGetLastError();
 }
 
-hipError_t nn_head(const float* a3, const float* P, int n_sets, const float* mean, const float* stdv, float* y_phys,
-                   const float* y_true, float* dy, float* sq, hipStream_t s)
+hipError_t nn_head(const uint16_t* s_bf, const uint16_t* W3bf, const float* P, int n_sets, const float* mean,
+                   const float* stdv, float* y_phys, hipStream_t s)
 {
-    hipLaunchKernelGGL(head_kernel, dim3(cdiv64(n_sets, 256)), dim3(256), 0, s, a3, P, n_sets, mean, stdv, y_phys,
-                       y_true, dy, sq);
+    hipLaunchKernelGGL((head_kernel<false>), dim3(cdiv64(n_sets, 32)), dim3(256), 0, s, s_bf, W3bf, P, n_sets, mean, stdv,
+                       y_phys, nullptr, nullptr, nullptr);
     return hipGetLastError();
 }
 
-hipError_t nn_head_back(const float* dy, const float* P, const float* z3, int n_sets, float* dz3, uint16_t* dz3_bf,
-                        hipStream_t s)
+// workgroups (and parts of the gradient) of the training kernels
+int nn_parts_head(int n_sets) { return cdiv64(n_sets, 32) < 64 ? cdiv64(n_sets, 32) : 64; }
+int nn_parts_phi(int n_sets) { return n_sets < 256 ? n_sets : 256; }
+
+hipError_t nn_head_train(const uint16_t* s_bf, const uint16_t* W3bf, const float* P, int n_sets, const float* mean,
+                         const float* stdv, const float* y_true, float* ds, float* part, hipStream_t s)
 {
-    hipLaunchKernelGGL(head_back_kernel, dim3(cdiv64((int64_t)n_sets * 128, 256)), dim3(256), 0, s, dy, P, z3, n_sets,
-                       dz3, dz3_bf);
+    hipLaunchKernelGGL((head_kernel<true>), dim3(nn_parts_head(n_sets)), dim3(256), 0, s, s_bf, W3bf, P, n_sets, mean, stdv,
+                       nullptr, y_true, ds, part);
     return hipGetLastError();
 }
 
-hipError_t nn_dz2(const float* ds, const float* z2, const int32_t* offsets, int n_sets, int64_t rows, float pool_scale,
-                  float* dz2, uint16_t* dz2_bf, hipStream_t s)
+hipError_t nn_phi_back(const float* x, const int32_t* offsets, int n_sets, const float* P, const uint16_t* W2bf,
+                       const float* ds, float pool_scale, float* part, hipStream_t s)
 {
-    hipLaunchKernelGGL(dz2_kernel, dim3(cdiv64(rows * 128, 256)), dim3(256), 0, s, ds, z2, offsets, n_sets, rows,
-                       pool_scale, dz2, dz2_bf);
+    hipLaunchKernelGGL(phi_back_kernel, dim3(nn_parts_phi(n_sets)), dim3(256), 0, s, x, offsets, n_sets, P, W2bf, ds,
+                       pool_scale, part);
     return hipGetLastError();
 }
 
-hipError_t nn_colsum(const float* in, int64_t rows, int cols, float* out, hipStream_t s)
+hipError_t nn_grad_sum(const float* part_phi, const float* part_head, int n_sets, float* G, float* loss, hipStream_t s)
 {
-    hipLaunchKernelGGL(colsum_kernel, dim3(cols), dim3(256), 0, s, in, rows, cols, out);
-    return hipGetLastError();
-}
-
-hipError_t nn_dw4(const float* dy, const float* a3, int n_sets, float* g, hipStream_t s)
-{
-    hipLaunchKernelGGL(dw4_kernel, dim3(NN_DOUT * 128), dim3(256), 0, s, dy, a3, n_sets, g);
-    return hipGetLastError();
-}
-
-hipError_t nn_dw1(const float* dh1, const float* x, const float* P, int64_t rows, float* g, hipStream_t s)
-{
-    hipLaunchKernelGGL(dw1_kernel, dim3(128), dim3(256), 0, s, dh1, x, P, rows, g);
-    return hipGetLastError();
-}
-
-hipError_t nn_loss(const float* sq, int n, float* loss, hipStream_t s)
-{
-    hipLaunchKernelGGL(loss_kernel, dim3(1), dim3(256), 0, s, sq, n, loss);
+    hipLaunchKernelGGL(grad_sum_kernel, dim3(NN_NPARAM / 64 + 1), dim3(256), 0, s, part_phi, nn_parts_phi(n_sets), part_head,
+                       nn_parts_head(n_sets), n_sets * NN_DOUT, G, loss);
     return hipGetLastError();
 }
 

@@ -226,3 +226,41 @@ def test_forward_of_many_sets_is_per_set(ctx):
         ref, _ = N.forward(p, xs, offs, 1.0 / 500, bf16_ops=True)
         assert rel(got[lo:hi].astype(np.float64), ref) <= 1e-3
     assert np.all(np.isfinite(got))
+
+
+@pytest.mark.parametrize("n_sets,most", [(33, 200), (300, 90), (2100, 40)])
+def test_gradients_of_many_sets(ctx, n_sets, most):
+    """Gradients over more sets than one workgroup of the head takes (32), than
+    workgroups of the bubbles' backward part (256) and of the head (64 x 32),
+    with set sizes around its groups of 64: the bars of the small batch."""
+    import torch
+    say("nn grads, many sets", n_sets)
+    rng = np.random.default_rng(n_sets)
+    sizes = rng.integers(0, most, size=n_sets)
+    sizes[:6] = [0, 1, 63, 64, 65, 129]
+    p, x, off, t = problem(6, list(sizes))
+    net = gpu_net(ctx, p, 1.0 / 500)
+    g = torch.zeros(N.param_count(), dtype=torch.float32, device="cuda")
+    loss = torch.zeros(1, dtype=torch.float32, device="cuda")
+    net.grads(dev(x), dev(off), dev(t), g, loss)
+    lref, gref = N.loss_and_grads(p, x, off, 1.0 / 500, t, bf16_ops=True)
+    assert abs(loss.item() / lref - 1) <= 1e-4
+    gg = N.unflatten(g.cpu().numpy().astype(np.float64))
+    for k in gref:
+        assert rel(gg[k], gref[k]) <= 1e-3, (k, rel(gg[k], gref[k]))
+
+
+def test_forward_of_unaligned_rows(ctx):
+    """Inputs that start four bytes past an aligned address give the same
+    outputs bit for bit."""
+    import torch
+    p, x, off, _ = problem(2, [500, 64, 65, 1, 257])
+    net = gpu_net(ctx, p, 1.0 / 500)
+    buf = torch.empty(x.size + 1, dtype=torch.float32, device="cuda")
+    xs = buf[1:].view(x.shape)
+    xs.copy_(dev(x))
+    assert xs.data_ptr() % 16 == 4
+    y, ys = (torch.empty((5, 5), dtype=torch.float32, device="cuda") for _ in range(2))
+    net.forward(dev(x), dev(off), y)
+    net.forward(xs, dev(off), ys)
+    assert torch.equal(y, ys)
