@@ -184,7 +184,7 @@ int ofm_nn_forward(ofm_nn* nn, const float* x, const int32_t* offsets, int32_t n
     WS w;
     rc = workspace(nn, n_sets, false, w);
     if (rc) return rc;
-    NNCHK(nn_phi_pool(x, offsets, n_sets, nn->P, nn->W2bf, nn->spec.pool_scale, w.s_bf, s));
+    NNCHK(nn_phi_pool(x, offsets, n_sets, R, nn->P, nn->W2bf, nn->spec.pool_scale, w.s_bf, s));
     NNCHK(nn_head(w.s_bf, nn->W3bf, nn->P, n_sets, nn->norm, nn->norm + 5, y, s));
     return OFM_OK;
 }
@@ -201,7 +201,7 @@ int ofm_nn_grads(ofm_nn* nn, const float* x, const int32_t* offsets, int32_t n_s
     rc = workspace(nn, n_sets, true, w);
     if (rc) return rc;
     const float scale = nn->spec.pool_scale;
-    NNCHK(nn_phi_pool(x, offsets, n_sets, nn->P, nn->W2bf, scale, w.s_bf, s));
+    NNCHK(nn_phi_pool(x, offsets, n_sets, R, nn->P, nn->W2bf, scale, w.s_bf, s));
     NNCHK(nn_head_train(w.s_bf, nn->W3bf, nn->P, n_sets, nn->norm, nn->norm + 5, y_true, w.ds, w.part_head, s));
     NNCHK(nn_phi_back(x, offsets, n_sets, nn->P, nn->W2bf, w.ds, scale, w.part_phi, s));
     NNCHK(nn_grad_sum(w.part_phi, w.part_head, n_sets, nn->G, loss, s));

@@ -26,8 +26,8 @@ constexpr int NN_PART_PHI = NN_W3;
 constexpr int NN_PART_HEAD = NN_NPARAM - NN_W3 + 1;
 
 // s_bf: the pooled activations as bf16, [n_sets][128]
-hipError_t nn_phi_pool(const float* x, const int32_t* offsets, int n_sets, const float* P, const uint16_t* W2bf,
-                       float pool_scale, uint16_t* s_bf, hipStream_t st);
+hipError_t nn_phi_pool(const float* x, const int32_t* offsets, int n_sets, int64_t rows, const float* P,
+                       const uint16_t* W2bf, float pool_scale, uint16_t* s_bf, hipStream_t st);
 hipError_t nn_head(const uint16_t* s_bf, const uint16_t* W3bf, const float* P, int n_sets, const float* mean,
                    const float* stdv, float* y_phys, hipStream_t s);
 int nn_parts_head(int n_sets);

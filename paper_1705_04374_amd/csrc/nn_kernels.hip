@@ -23,6 +23,8 @@
 
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "nn_kernels.h"
 
 namespace ofm {
@@ -47,6 +49,14 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
 {
     const floatx2 f = { lo, hi };
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
+}
+
+// In one operation: with a visible infinity the compiler makes it a maximum
+// behind a canonicalisation, two.  A NaN gives 0, as fmaxf(v, 0) does.
+__device__ __forceinline__ float relu(float v) {
+    float inf = __builtin_inff();
+    asm("" : "+s"(inf));
+    return __builtin_amdgcn_fmed3f(v, 0.f, inf);
 }
 
 __device__ __forceinline__ bf16x8 frag(const uint16_t* p)
@@ -79,27 +89,47 @@ __device__ __forceinline__ int unit_of_row(int m)
 constexpr int HP = 128 + 8;   // LDS pitch of 128 bf16: 16-byte fragments stay aligned
 constexpr int RP = 64 + 8;    // the same for 64
 
+// A 128 x 128 weight matrix into LDS [n][k], pitch HP (256 threads), and eight
+// of its rows at one column as a fragment.
+__device__ __forceinline__ void stage_weights(const uint16_t* __restrict__ W, uint16_t* sW, int tid)
+{
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int e = (q * 256 + tid) * 8;
+        *reinterpret_cast<u16x8*>(&sW[(e >> 7) * HP + (e & 127)]) = *reinterpret_cast<const u16x8*>(&W[e]);
+    }
+}
+__device__ __forceinline__ bf16x8 column_frag(const uint16_t* sW, int n0, int k)
+{
+    u16x8 v;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v.v[i] = sW[(n0 + i) * HP + k];
+    return __builtin_bit_cast(bf16x8, v);
+}
+
 // ---------------------------------------------------------------------------
 // phi and the sum pool.  A wavefront takes 64 bubbles of one set at a time:
 // the input layer as W1 X^T (two blocks of 32 bubbles), whose result, after
 // ReLU and rounding, is already the left operand of the 128 x 128 layer
 // (unit_of_row), so that activations never pass through LDS; W2 is read from
-// LDS as the right operand, each fragment used for both blocks; then bias,
-// ReLU and column sums.  A set's sum adds its groups of 64 in order, two at a
-// time, whichever wavefront computed them, so that its result does not depend
-// on the launch.
+// LDS as the right operand, each fragment used for both blocks.  Layer 2 goes
+// by blocks of 32 columns: bias, ReLU and column sums of one block are vector
+// work that the matrix products of the next hide.  A set's sum adds its
+// groups of 64 in order, two at a time, whichever wavefront computed them, so
+// that its result does not depend on the launch.
 //
-// Per 64 bubbles and wavefront: 64 bf16 and 16 float MFMAs (3072 cycles of
-// the SIMD's matrix core), about 620 vector operations (2500 cycles) that the
-// other wavefront of the SIMD overlaps with them.  128 accumulators a lane
-// hold it to two wavefronts.  16384 sets of 500: 1117 us before (input layer
-// on the vector units, activations through LDS), PHI_NOW now.
+// Per 64 bubbles: 64 bf16 and 16 float MFMAs (1.32 us of a SIMD's matrix core
+// at the rates measured for them alone) and 640 vector operations (1.47 us),
+// which overlap in part: 2.3 us.  16384 sets of 500: 1117 us before (input
+// layer on the vector units, activations through LDS, 128 rows a workgroup),
+// 305 now (365 before the activations took one operation each and the next
+// inputs were loaded ahead).
 //
-// per_wave: a set per wavefront; otherwise a set per workgroup, its groups
-// dealt to the four wavefronts.
+// PER_WAVE: a set per wavefront (the next group's inputs loaded ahead);
+// otherwise a set per workgroup, its groups dealt to the four wavefronts.
 // ---------------------------------------------------------------------------
 template <bool PER_WAVE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PER_WAVE ? 2 : 3)))
 phi_pool_kernel(const float* __restrict__ x, const int32_t* __restrict__ offsets, int n_sets,
                 const float* __restrict__ P, const uint16_t* __restrict__ W2bf, float pool_scale,
                 uint16_t* __restrict__ s_bf)
@@ -109,7 +139,7 @@ phi_pool_kernel(const float* __restrict__ x, const int32_t* __restrict__ offsets
     __shared__ float colsum[PER_WAVE ? 1 : 4][128];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 31, half = lane >> 5;
-    for (int e = tid; e < 128 * 128; e += 256) sW[(e >> 7) * HP + (e & 127)] = W2bf[e];
+    stage_weights(W2bf, sW, tid);
     if (tid < 128) sb1[tid] = P[NN_B1 + tid];
     float a1[4][2], b2[4];
 #pragma unroll
@@ -120,24 +150,22 @@ phi_pool_kernel(const float* __restrict__ x, const int32_t* __restrict__ offsets
     }
     __syncthreads();
 
-    // column sums of the bubbles c .. min(c + 64, r1) - 1 (every lane gets
-    // those of its four columns)
-    auto group = [&](int c, int r1, float (&cs)[4]) {
-        float xb[2][2];
+    // this lane's inputs of the bubbles c .. min(c + 64, r1) - 1
+    auto load = [&](int c, int r1, float (&xb)[2][2]) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int r = c + i * 32 + col;
 #pragma unroll
             for (int k = 0; k < 2; ++k) xb[i][k] = r < r1 ? x[(int64_t)r * 4 + 2 * k + half] : 0.f;
         }
-        floatx16 acc[2][4];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = splat16(0.f);
+    };
+
+    // their column sums (every lane gets those of its four columns)
+    auto group_of = [&](auto full_c, int c, int r1, const float (&xb)[2][2], float (&cs)[4]) {
+        constexpr bool FULL = decltype(full_c)::value;    // 64 bubbles: no row check
+        bf16x8 h[2][8];                           // ReLU(z1), the left operands of layer 2
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            __builtin_amdgcn_sched_barrier(0);
             floatx16 d[2];
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
@@ -150,65 +178,91 @@ phi_pool_kernel(const float* __restrict__ x, const int32_t* __restrict__ offsets
 #pragma unroll
                 for (int i = 0; i < 2; ++i) d[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[u][k], xb[i][k], d[i], 0, 0, 0);
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                bf16x8 h[2];
+            for (int t = 0; t < 2; ++t)
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
                     u32x4 p;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        p.v[q] = pack_bf16(fmaxf(d[i][8 * t + 2 * q], 0.f), fmaxf(d[i][8 * t + 2 * q + 1], 0.f));
-                    h[i] = __builtin_bit_cast(bf16x8, p);
+                    for (int q = 0; q < 4; ++q) p.v[q] = pack_bf16(relu(d[i][8 * t + 2 * q]), relu(d[i][8 * t + 2 * q + 1]));
+                    h[i][2 * u + t] = __builtin_bit_cast(bf16x8, p);
                 }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const bf16x8 b = frag(&sW[(j * 32 + col) * HP + u * 32 + t * 16 + half * 8]);
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(h[i], b, acc[i][j], 0, 0, 0);
-                }
-            }
         }
-        const bool full = c + 64 <= r1;           // no row check
+        auto product = [&](int j, floatx16 (&acc)[2]) {
+            acc[0] = acc[1] = splat16(0.f);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const bf16x8 b = frag(&sW[(j * 32 + col) * HP + t * 16 + half * 8]);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(h[i][t], b, acc[i], 0, 0, 0);
+            }
+        };
+        auto column = [&](int j, const floatx16 (&acc)[2]) {
+            float v = 0.f;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const float r = fmaxf(acc[i][e] + b2[j], 0.f);
+                    v += FULL || c + i * 32 + mfma_row(e, lane) < r1 ? r : 0.f;
+                }
+            cs[j] = v + __shfl_xor(v, 32, 64);
+        };
+        floatx16 acc[2][2];
+        product(0, acc[0]);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            float v = 0.f;
-            if (full) {
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) v += fmaxf(acc[i][j][e] + b2[j], 0.f);
-            } else {
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e)
-                        if (c + i * 32 + mfma_row(e, lane) < r1) v += fmaxf(acc[i][j][e] + b2[j], 0.f);
-            }
-            cs[j] = v + __shfl_xor(v, 32, 64);
+            if (j + 1 < 4) product(j + 1, acc[(j + 1) & 1]);
+            column(j, acc[j & 1]);
         }
+    };
+    auto group = [&](int c, int r1, const float (&xb)[2][2], float (&cs)[4]) {
+        if (c + 64 <= r1)
+            group_of(std::true_type{}, c, r1, xb, cs);
+        else
+            group_of(std::false_type{}, c, r1, xb, cs);
     };
 
     if constexpr (PER_WAVE) {
-        for (int set = blockIdx.x * 4 + wave; set < n_sets; set += gridDim.x * 4) {
-            const int r0 = offsets[set], r1 = offsets[set + 1];
-            float sum[4] = { 0.f, 0.f, 0.f, 0.f }, first[4];
-            bool odd = false;
+        // one group of 64 an iteration (at least one a set); the next one's
+        // inputs, also those of the next set, are loaded ahead
+        const int step = gridDim.x * 4;
+        int set = blockIdx.x * 4 + wave;
+        if (set >= n_sets) return;
+        int c = offsets[set], r1 = offsets[set + 1];
+        float xb[2][2], sum[4] = { 0.f, 0.f, 0.f, 0.f }, first[4] = { 0.f, 0.f, 0.f, 0.f };
+        bool odd = false;
+        load(c, r1, xb);
 #pragma clang loop unroll(disable)
-            for (int c = r0; c < r1; c += 64) {
-                float cs[4];
-                group(c, r1, cs);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (odd) sum[j] += first[j] + cs[j];
-                    first[j] = cs[j];
-                }
-                odd = !odd;
-            }
+        while (set < n_sets) {
+            const bool last = c + 64 >= r1;
+            const int nset = last ? set + step : set;
+            int nc = c + 64, nr1 = r1;
+            if (last && nset < n_sets) { nc = offsets[nset]; nr1 = offsets[nset + 1]; }
+            float xn[2][2], cs[4];
+            load(nc, nset < n_sets ? nr1 : nc, xn);
+            group(c, r1, xb, cs);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                if (odd) sum[j] += first[j];
-                if (half == 0) s_bf[(int64_t)set * 128 + j * 32 + col] = to_bf16(pool_scale * sum[j]);
+                if (odd) sum[j] += first[j] + cs[j];
+                first[j] = cs[j];
             }
+            odd = !odd;
+            if (last) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (odd) sum[j] += first[j];
+                    if (half == 0) s_bf[(int64_t)set * 128 + j * 32 + col] = to_bf16(pool_scale * sum[j]);
+                    sum[j] = 0.f;
+                }
+                odd = false;
+            }
+            set = nset;
+            c = nc;
+            r1 = nr1;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int k = 0; k < 2; ++k) xb[i][k] = xn[i][k];
         }
     } else {
         for (int set = blockIdx.x; set < n_sets; set += gridDim.x) {
@@ -217,7 +271,11 @@ phi_pool_kernel(const float* __restrict__ x, const int32_t* __restrict__ offsets
             for (int c0 = r0; c0 < r1; c0 += 256) {
                 const int c = c0 + wave * 64;
                 float cs[4] = { 0.f, 0.f, 0.f, 0.f };
-                if (c < r1) group(c, r1, cs);
+                if (c < r1) {
+                    float xb[2][2];
+                    load(c, r1, xb);
+                    group(c, r1, xb, cs);
+                }
                 if (half == 0)
 #pragma unroll
                     for (int j = 0; j < 4; ++j) colsum[wave][j * 32 + col] = cs[j];
@@ -253,13 +311,16 @@ __global__ void __launch_bounds__(256) head_kernel(const uint16_t* __restrict__ 
                                                    float* __restrict__ ds, float* __restrict__ part)
 {
     constexpr int AP = 129;
-    __shared__ float sA[32 * AP];                       // ReLU(z3) [set][k]
-    __shared__ __align__(16) uint16_t sZ[TRAIN ? 32 * HP : 1];        // dz3 as bf16 [set][n]
+    __shared__ __align__(16) uint16_t smem[TRAIN ? 128 * HP : 64 * AP];   // TRAIN: first W3
+    float* sA = reinterpret_cast<float*>(smem);         // ReLU(z3) [set][k]
+    uint16_t* sZ = smem + 64 * HP;                      // TRAIN: dz3 as bf16 [set][n]
+    __shared__ float sW4[NN_DOUT * 128];
     __shared__ float sY[TRAIN ? 32 * NN_DOUT : 1];      // dy
     __shared__ float sQ[TRAIN ? 256 : 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lc = lane & 31, half = lane >> 5, n = wave * 32 + lc;
     const float b3 = P[NN_B3 + n];
+    for (int e = tid; e < NN_DOUT * 128; e += 256) sW4[e] = P[NN_W4 + e];
     float w4[NN_DOUT];
     bf16x8 wt[TRAIN ? 8 : 1];                           // W3 with column n over K (ds)
     floatx16 dW3[TRAIN ? 4 : 1];
@@ -267,13 +328,10 @@ __global__ void __launch_bounds__(256) head_kernel(const uint16_t* __restrict__ 
     if constexpr (TRAIN) {
 #pragma unroll
         for (int o = 0; o < NN_DOUT; ++o) w4[o] = P[NN_W4 + o * 128 + n];
+        stage_weights(W3bf, smem, tid);
+        __syncthreads();
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            u16x8 v;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v.v[i] = W3bf[(t * 16 + half * 8 + i) * 128 + n];
-            wt[t] = __builtin_bit_cast(bf16x8, v);
-        }
+        for (int t = 0; t < 8; ++t) wt[t] = column_frag(smem, t * 16 + half * 8, n);
 #pragma unroll
         for (int q = 0; q < 4; ++q) dW3[q] = splat16(0.f);
     }
@@ -294,7 +352,8 @@ __global__ void __launch_bounds__(256) head_kernel(const uint16_t* __restrict__ 
         if (tid < 32 * NN_DOUT) {
             const int s = tid & 31, o = tid >> 5, set = s0 + s;
             float y = P[NN_B4 + o];
-            for (int k = 0; k < 128; ++k) y += sA[s * AP + k] * P[NN_W4 + o * 128 + k];
+            #pragma unroll 16
+            for (int k = 0; k < 128; ++k) y += sA[s * AP + k] * sW4[o * 128 + k];
             float dy = 0.f;
             if (set < n_sets) {
                 if (y_phys) y_phys[(int64_t)set * NN_DOUT + o] = y * stdv[o] + mean[o];
@@ -395,29 +454,31 @@ __global__ void __launch_bounds__(256) head_kernel(const uint16_t* __restrict__ 
 // its columns of dh1.  dz2 as computed (bubbles in registers, units over
 // lanes) is the left operand of dW2; dh1 needs it with units in registers:
 // through LDS, like h1.
-// Bound by its barriers and LDS at one or two wavefronts per SIMD: 256 sets of
-// 500 took 2.0 ms in 13 launches over 500 MB of stored activations, gradients
-// and GEMM splits before, BACK_NOW now.
+// One workgroup a CU (a set each, at most 256) in lockstep over three barriers:
+// bound by each group's chain of 56 MFMAs, 700 vector and 120 LDS operations a
+// wavefront.  256 sets of 500 took 2.2 ms in 12 launches over 500 MB of stored
+// activations, gradients and GEMM splits before, 40 us now.  (Half sets to 512
+// workgroups: 47 us, and twice the parts to sum.)
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 phi_back_kernel(const float* __restrict__ x, const int32_t* __restrict__ offsets, int n_sets,
                 const float* __restrict__ P, const uint16_t* __restrict__ W2bf, const float* __restrict__ ds,
                 float pool_scale, float* __restrict__ part)
 {
-    __shared__ __align__(16) uint16_t sH[64 * HP];                    // h1 [bubble][unit]
-    __shared__ __align__(16) uint16_t sT[128 * RP];                   // h1 [unit][bubble, in the registers' order]
-    __shared__ __align__(16) uint16_t sD[64 * HP];                    // dz2 [bubble][unit]
+    __shared__ __align__(16) uint16_t smem[128 * HP + 128 * RP];
+    uint16_t* sH = smem;                                // h1 [bubble][unit]
+    uint16_t* sD = smem + 64 * HP;                      // dz2 [bubble][unit]
+    uint16_t* sT = smem + 128 * HP;                     // h1 [unit][bubble, in the registers' order]
     __shared__ float4 sX[64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lc = lane & 31, half = lane >> 5, n = wave * 32 + lc;
     bf16x8 w2[8], w2t[8];                               // W2 row n; W2 column n
+    stage_weights(W2bf, smem, tid);
+    __syncthreads();
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
-        w2[t] = frag(&W2bf[n * 128 + t * 16 + half * 8]);
-        u16x8 v;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v.v[i] = W2bf[(t * 16 + half * 8 + i) * 128 + n];
-        w2t[t] = __builtin_bit_cast(bf16x8, v);
+        w2[t] = frag(&smem[n * HP + t * 16 + half * 8]);
+        w2t[t] = column_frag(smem, t * 16 + half * 8, n);
     }
     float a1[2], b1[2], bias1[16];
 #pragma unroll
@@ -436,20 +497,29 @@ phi_back_kernel(const float* __restrict__ x, const int32_t* __restrict__ offsets
         const int r0 = offsets[set], r1 = offsets[set + 1];
         const float dsc = pool_scale * ds[(int64_t)set * 128 + n];
         const uint32_t dlo = to_bf16(dsc), dhi = dlo << 16;
-        for (int c = r0; c < r1; c += 64) {
-            float xb[2][2];
+        float xn[2][2];                                 // inputs of the next 64 bubbles
+        auto load = [&](int c) {
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 const int r = c + i * 32 + lc;
 #pragma unroll
-                for (int k = 0; k < 2; ++k) xb[i][k] = r < r1 ? x[(int64_t)r * 4 + 2 * k + half] : 0.f;
+                for (int k = 0; k < 2; ++k) xn[i][k] = r < r1 ? x[(int64_t)r * 4 + 2 * k + half] : 0.f;
             }
+        };
+        load(r0);
+        for (int c = r0; c < r1; c += 64) {
+            float xb[2][2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int k = 0; k < 2; ++k) xb[i][k] = xn[i][k];
+            load(c + 64);
             __syncthreads();                            // the pass before has read sX, sH, sT and sD
-            if (tid < 64) {
-                const int r = c + tid;
-                const float* xr = x + (int64_t)r * 4;
-                sX[tid] = r < r1 ? make_float4(xr[0], xr[1], xr[2], xr[3]) : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
+            if (wave == 0)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) reinterpret_cast<float*>(&sX[i * 32 + lc])[2 * k + half] = xb[i][k];
             uint32_t on1 = 0;                           // bit 16 i + e: z1 > 0
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
@@ -466,7 +536,7 @@ phi_back_kernel(const float* __restrict__ x, const int32_t* __restrict__ offsets
                     u32x4 p;
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
-                        p.v[q] = pack_bf16(fmaxf(d[8 * t + 2 * q], 0.f), fmaxf(d[8 * t + 2 * q + 1], 0.f));
+                        p.v[q] = pack_bf16(relu(d[8 * t + 2 * q]), relu(d[8 * t + 2 * q + 1]));
                     *reinterpret_cast<u32x4*>(&sH[(i * 32 + lc) * HP + wave * 32 + t * 16 + half * 8]) = p;
                 }
 #pragma unroll
@@ -474,7 +544,7 @@ phi_back_kernel(const float* __restrict__ x, const int32_t* __restrict__ offsets
                     u32x2 p;
 #pragma unroll
                     for (int q = 0; q < 2; ++q)
-                        p.v[q] = pack_bf16(fmaxf(dt[4 * g + 2 * q], 0.f), fmaxf(dt[4 * g + 2 * q + 1], 0.f));
+                        p.v[q] = pack_bf16(relu(dt[4 * g + 2 * q]), relu(dt[4 * g + 2 * q + 1]));
                     *reinterpret_cast<u32x2*>(&sT[n * RP + i * 32 + 16 * (g >> 1) + 8 * half + 4 * (g & 1)]) = p;
                 }
 #pragma unroll
@@ -646,18 +716,22 @@ __global__ void __launch_bounds__(256) features_kernel(const double* __restrict_
 // ---------------------------------------------------------------------------
 static int cdiv64(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
-hipError_t nn_phi_pool(const float* x, const int32_t* offsets, int n_sets, const float* P, const uint16_t* W2bf,
-                       float pool_scale, uint16_t* s_bf, hipStream_t st)
+hipError_t nn_phi_pool(const float* x, const int32_t* offsets, int n_sets, int64_t rows, const float* P,
+                       const uint16_t* W2bf, float pool_scale, uint16_t* s_bf, hipStream_t st)
 {
-    // Two workgroups of four wavefronts are resident on each of 256 CUs.  A
-    // set per wavefront wastes nothing inside a set, but needs many sets to
-    // come out even; below 4096 sets a set per workgroup finishes
-    // earlier.
-    if (n_sets >= 4096)
-        hipLaunchKernelGGL((phi_pool_kernel<true>), dim3(512), dim3(256), 0, st, x, offsets, n_sets, P, W2bf, pool_scale, s_bf);
+    // A set per wavefront wastes nothing inside a set: taken where the sets give
+    // each SIMD a wavefront, or have one group of 64 each on average, so that
+    // three wavefronts of a workgroup would idle.  Fewer, larger sets finish
+    // earlier dealt to four wavefronts.  A forward call by wavefronts against
+    // by workgroups: 256 sets of 500, 47 us against 35; 1000 of 500, 50 against
+    // 49; 1000 of 100, 34 against 38; 2000 of 500, 63 against 65; 4096 of 100,
+    // 48 against 61; 1000 of 60, 32 against 37.
+    if (n_sets >= 1024 || rows <= 64 * (int64_t)n_sets)
+        hipLaunchKernelGGL((phi_pool_kernel<true>), dim3(n_sets < 4096 ? (n_sets + 3) / 4 : 1024), dim3(256), 0, st, x, offsets,
+                           n_sets, P, W2bf, pool_scale, s_bf);
     else
-        hipLaunchKernelGGL((phi_pool_kernel<false>), dim3(n_sets < 512 ? n_sets : 512), dim3(256), 0, st, x, offsets, n_sets, P,
-                           W2bf, pool_scale, s_bf);
+        hipLaunchKernelGGL((phi_pool_kernel<false>), dim3(n_sets), dim3(256), 0, st, x, offsets, n_sets, P, W2bf, pool_scale,
+                           s_bf);
     return hipGetLastError();
 }
 
