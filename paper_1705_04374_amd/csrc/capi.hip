@@ -192,6 +192,7 @@ struct ofm_run {
     ofm::TilePartial* d_part = nullptr;
     double* d_dt = nullptr;
     ofm::WorkItem* d_work = nullptr;
+    int most_tiles = 0;         // of a member
     std::vector<int> order;                 // samples, larger grids first
     int64_t dts_len = 0;
     hipGraph_t graph = nullptr;
@@ -244,7 +245,7 @@ static int run_capture(ofm_run& r)
             r.la.src = (g + stg) & 1;     // replayed at even step indices only
             hipError_t le = launch_stage(s0.precision, s0.ndim, r.tc.tx, r.tc.ty, r.la, stg, stream);
             if (le == hipSuccess && stg == 2)
-                le = launch_finalize(r.d_desc, r.d_state, r.d_part, ns, 0, r.d_dt, r.dts_len, stream);
+                le = launch_finalize(r.d_desc, r.d_state, r.d_part, ns, r.most_tiles, 0, r.d_dt, r.dts_len, stream);
             if (le != hipSuccess) rc = fail(ctx, OFM_EHIP, "launch failed: %s", hipGetErrorString(le));
         }
     hipError_t ce = hipStreamEndCapture(stream, &r.graph);
@@ -305,24 +306,28 @@ static int run_begin(ofm_ctx* ctx, ofm_run& r, bool init, int64_t dts_len, hipSt
             return fail(ctx, OFM_EINVAL, "batched items with the far-field boundary must share p_inf");
     }
     // tiling
-    int maxn = 0;
-    for (const Member& m : mem) maxn = std::max(maxn, m.spec.n);
-    r.tc = ctx->tuning.choose(prec, nd, maxn, ns);
+    std::vector<int> sizes;
+    for (const Member& m : mem) sizes.push_back(m.spec.n);
+    r.tc = ctx->tuning.choose(prec, nd, sizes);
     const TileChoice& tc = r.tc;
     r.desc.assign(ns, SampleDesc{});
     int tiles = 0;
     for (int i = 0; i < ns; ++i) {
         r.desc[i] = make_desc(mem[i].spec, tc, tiles, mem[i].buf0, mem[i].buf1, mem[i].du);
         tiles += r.desc[i].ntiles;
+        r.most_tiles = std::max(r.most_tiles, r.desc[i].ntiles);
     }
-    // work list: larger samples first, tiles of a sample contiguous
+    // work list: larger samples first, tiles of a sample contiguous (one
+    // sample needs none)
     r.order.resize(ns);
     for (int i = 0; i < ns; ++i) r.order[i] = i;
     std::stable_sort(r.order.begin(), r.order.end(), [&](int a, int b) { return mem[a].spec.n > mem[b].spec.n; });
     std::vector<WorkItem> work;
-    work.reserve(tiles);
-    for (int i : r.order)
-        for (int t = 0; t < r.desc[i].ntiles; ++t) work.push_back(WorkItem{ i, t });
+    if (ns > 1) {
+        work.reserve(tiles);
+        for (int i : r.order)
+            for (int t = 0; t < r.desc[i].ntiles; ++t) work.push_back(WorkItem{ i, t });
+    }
 
     const size_t o_desc = 0;
     const size_t o_state = align256(o_desc + sizeof(SampleDesc) * ns);
@@ -352,14 +357,15 @@ static int run_begin(ofm_ctx* ctx, ofm_run& r, bool init, int64_t dts_len, hipSt
     r.d_desc = (SampleDesc*)(meta + o_desc);
     r.d_state = (SampleState*)(meta + o_state);
     r.d_part = (TilePartial*)(meta + o_part);
-    WorkItem* d_work = r.d_work = (WorkItem*)(meta + o_work);
+    r.d_work = ns > 1 ? (WorkItem*)(meta + o_work) : nullptr;
     r.d_dt = dts_len > 0 ? (double*)(meta + o_dt) : nullptr;
 
     std::vector<SampleState> st0(ns);
     for (auto& s : st0) memset(&s, 0, sizeof s);
     HIPCHK(ctx, hipMemcpyAsync(r.d_desc, r.desc.data(), sizeof(SampleDesc) * ns, hipMemcpyHostToDevice, stream));
     HIPCHK(ctx, hipMemcpyAsync(r.d_state, st0.data(), sizeof(SampleState) * ns, hipMemcpyHostToDevice, stream));
-    HIPCHK(ctx, hipMemcpyAsync(d_work, work.data(), sizeof(WorkItem) * work.size(), hipMemcpyHostToDevice, stream));
+    if (ns > 1)
+        HIPCHK(ctx, hipMemcpyAsync(r.d_work, work.data(), sizeof(WorkItem) * work.size(), hipMemcpyHostToDevice, stream));
 
     hipEvent_t e0, e1;
     HIPCHK(ctx, hipEventCreate(&e0));
@@ -398,8 +404,8 @@ static int run_begin(ofm_ctx* ctx, ofm_run& r, bool init, int64_t dts_len, hipSt
     }
     LaunchArgs& la = r.la;
     la.ph = ph;
-    la.work = d_work;
-    la.n_work = (int)work.size();
+    la.work = r.d_work;
+    la.n_work = tiles;
     la.zchunk = tc.zchunk;
     la.desc = r.d_desc;
     la.state = r.d_state;
@@ -407,7 +413,7 @@ static int run_begin(ofm_ctx* ctx, ofm_run& r, bool init, int64_t dts_len, hipSt
     la.bc = bc;
     la.src = 0;
     HIPCHK(ctx, launch_reduce(prec, nd, tc.tx, tc.ty, la, stream));
-    HIPCHK(ctx, launch_finalize(r.d_desc, r.d_state, r.d_part, ns, 1, r.d_dt, dts_len, stream));
+    HIPCHK(ctx, launch_finalize(r.d_desc, r.d_state, r.d_part, ns, r.most_tiles, 1, r.d_dt, dts_len, stream));
     HIPCHK(ctx, hipEventRecord(e1, stream));
     HIPCHK(ctx, hipEventSynchronize(e1));
     r.init_s = elapsed_s(e0, e1);
@@ -454,7 +460,7 @@ static int run_enqueue(ofm_run& r, int nsteps, int64_t g0)
                 ctx->t_cells += r.live_cells;
             }
             if (stg == 2)
-                HIPCHK(ctx, launch_finalize(r.d_desc, r.d_state, r.d_part, ns, 0, r.d_dt, r.dts_len, stream));
+                HIPCHK(ctx, launch_finalize(r.d_desc, r.d_state, r.d_part, ns, r.most_tiles, 0, r.d_dt, r.dts_len, stream));
         }
     return OFM_OK;
 }
@@ -599,19 +605,13 @@ static char* scratch_of(const ofm_ctx* ctx)
     return ctx->device < kMaxDevices ? g_scratch[ctx->device] : nullptr;
 }
 
-// Descriptor, a zeroed dynamic state and the work list (tiles 0..ntiles-1
-// of sample 0), written by the device from kernel arguments (no copies from
-// host memory).
-__global__ void __launch_bounds__(256) noalloc_setup_kernel(SampleDesc d, SampleDesc* dd, SampleState* ds,
-                                                            WorkItem* work, int ntiles)
+// Descriptor and a zeroed dynamic state, written by the device from kernel
+// arguments (no copies from host memory).
+__global__ void noalloc_setup_kernel(SampleDesc d, SampleDesc* dd, SampleState* ds)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i == 0) {
-        *dd = d;
-        SampleState z{};
-        *ds = z;
-    }
-    if (i < ntiles) work[i] = WorkItem{ 0, i };
+    *dd = d;
+    SampleState z{};
+    *ds = z;
 }
 
 }  // namespace ofm
@@ -756,14 +756,20 @@ int ofm_step_noalloc(ofm_ctx* ctx, const ofm_solve_spec* spec, ofm_state_view* s
     ofm_solve_spec s = *spec;
     s.n_steps = n_steps;
     s.max_steps = n_steps;
-    const TileChoice tc = ctx->tuning.choose(s.precision, s.ndim, s.n, 1);
-    const SampleDesc d = make_desc(s, tc, 0, st->u, st->u_tmp, st->du);
-    // scratch layout: descriptor | state | partials | work list | step sizes
+    // scratch layout: descriptor | state | partials | step sizes
     const size_t o_state = align256(sizeof(SampleDesc));
     const size_t o_part = align256(o_state + sizeof(SampleState));
-    const size_t o_work = align256(o_part + sizeof(TilePartial) * (size_t)d.ntiles);
-    const size_t o_dt = align256(o_work + sizeof(WorkItem) * (size_t)d.ntiles);
-    const size_t need = o_dt + (dts ? sizeof(double) * (size_t)n_steps : 0);
+    auto log_at = [&](const SampleDesc& d) { return align256(o_part + sizeof(TilePartial) * (size_t)d.ntiles); };
+    const size_t log_bytes = dts ? sizeof(double) * (size_t)n_steps : 0;
+    // a long log leaves room for few tiles: the tiling with fewer then
+    TileChoice tc = ctx->tuning.choose(s.precision, s.ndim, { s.n });
+    SampleDesc d = make_desc(s, tc, 0, st->u, st->u_tmp, st->du);
+    if (log_at(d) + log_bytes > (size_t)OFM_NOALLOC_SCRATCH_BYTES && !ctx->tuning.has(s.precision, s.ndim, s.n)) {
+        tc = Tuning::general(s.precision, s.ndim, s.n);
+        d = make_desc(s, tc, 0, st->u, st->u_tmp, st->du);
+    }
+    const size_t o_dt = log_at(d);
+    const size_t need = o_dt + log_bytes;
     if (need > (size_t)OFM_NOALLOC_SCRATCH_BYTES)
         return fail(ctx, OFM_EINVAL,
                     "ofm_step_noalloc: %d tiles%s need %zu bytes of scratch; the fixed scratch holds %zu",
@@ -774,16 +780,14 @@ int ofm_step_noalloc(ofm_ctx* ctx, const ofm_solve_spec* spec, ofm_state_view* s
     SampleDesc* d_desc = (SampleDesc*)base;
     SampleState* d_state = (SampleState*)(base + o_state);
     TilePartial* d_part = (TilePartial*)(base + o_part);
-    WorkItem* d_work = (WorkItem*)(base + o_work);
     double* d_dt = dts ? (double*)(base + o_dt) : nullptr;
     const int64_t dt_len = dts ? n_steps : 0;
     hipStream_t hs = (hipStream_t)stream;
-    hipLaunchKernelGGL(noalloc_setup_kernel, dim3((d.ntiles + 255) / 256), dim3(256), 0, hs, d, d_desc, d_state,
-                       d_work, d.ntiles);
+    hipLaunchKernelGGL(noalloc_setup_kernel, dim3(1), dim3(1), 0, hs, d, d_desc, d_state);
     HIPCHK(ctx, hipGetLastError());
     LaunchArgs la{};
     la.ph = make_phys(s);
-    la.work = d_work;
+    la.work = nullptr;
     la.n_work = d.ntiles;
     la.zchunk = tc.zchunk;
     la.desc = d_desc;
@@ -795,12 +799,12 @@ int ofm_step_noalloc(ofm_ctx* ctx, const ofm_solve_spec* spec, ofm_state_view* s
     // per step three stages (stage k of step g reads buffer (g + k) & 1) and
     // the finalisation
     HIPCHK(ctx, launch_reduce(s.precision, s.ndim, tc.tx, tc.ty, la, hs));
-    HIPCHK(ctx, launch_finalize(d_desc, d_state, d_part, 1, 1, d_dt, dt_len, hs));
+    HIPCHK(ctx, launch_finalize(d_desc, d_state, d_part, 1, d.ntiles, 1, d_dt, dt_len, hs));
     for (int64_t g = 0; g < n_steps; ++g)
         for (int stg = 0; stg < 3; ++stg) {
             la.src = (int)((g + stg) & 1);
             HIPCHK(ctx, launch_stage(s.precision, s.ndim, tc.tx, tc.ty, la, stg, hs));
-            if (stg == 2) HIPCHK(ctx, launch_finalize(d_desc, d_state, d_part, 1, 0, d_dt, dt_len, hs));
+            if (stg == 2) HIPCHK(ctx, launch_finalize(d_desc, d_state, d_part, 1, d.ntiles, 0, d_dt, dt_len, hs));
         }
     SampleState out;
     HIPCHK(ctx, hipMemcpyAsync(&out, d_state, sizeof out, hipMemcpyDeviceToHost, hs));
@@ -956,7 +960,7 @@ int ofm_tune_get(const ofm_ctx* ctx, int32_t precision, int32_t ndim, int32_t n,
     if (!ctx || !out) return fail(nullptr, OFM_EINVAL, "ofm_tune_get: null argument");
     if (ndim < 1 || ndim > 3 || (precision != OFM_F32 && precision != OFM_F64) || n < 1)
         return fail(const_cast<ofm_ctx*>(ctx), OFM_EINVAL, "ofm_tune_get: bad precision, ndim or n");
-    const TileChoice t = ctx->tuning.choose(precision, ndim, n, 1);
+    const TileChoice t = ctx->tuning.choose(precision, ndim, { n });
     *out = ofm_tune_result{ t.tx, t.ty, t.zchunk, t.graph_steps, 0.0, 0, 0 };
     return OFM_OK;
 }
@@ -995,7 +999,7 @@ int ofm_autotune(ofm_ctx* ctx, const ofm_solve_spec* spec, ofm_state_view* st, i
         if (z.empty()) z.push_back(spec->n);
         return z;
     };
-    const TileChoice before = ctx->tuning.choose(spec->precision, spec->ndim, spec->n, 1);
+    const TileChoice before = ctx->tuning.choose(spec->precision, spec->ndim, { spec->n });
     const bool had_timing = ctx->timing;
     const int64_t l0 = ctx->t_launches;
     const double m0 = ctx->t_ms, c0 = ctx->t_cells;

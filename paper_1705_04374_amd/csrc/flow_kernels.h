@@ -24,8 +24,9 @@ hipError_t launch_stage(int precision, int ndim, int tx, int ty, const LaunchArg
 // at once (0 if unknown)
 int stage_blocks_per_cu(int precision, int ndim, int tx, int ty, int order);
 hipError_t launch_reduce(int precision, int ndim, int tx, int ty, const LaunchArgs& a, hipStream_t s);
+// most_tiles: of any of the samples
 hipError_t launch_finalize(const SampleDesc* desc, SampleState* state, const TilePartial* part, int n_samples,
-                           int initial, double* dt_log, int64_t dt_log_len, hipStream_t s);
+                           int most_tiles, int initial, double* dt_log, int64_t dt_log_len, hipStream_t s);
 hipError_t launch_init(int precision, int ndim, const InitLaunch& L, hipStream_t s);
 hipError_t launch_to_conserved(int precision, int ndim, const PhysD& ph, const void* u, double* q, int64_t ncell,
                                hipStream_t s);

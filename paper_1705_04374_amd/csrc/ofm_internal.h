@@ -63,14 +63,13 @@ struct TilePartial {
     double s_max;
     double p_max;
     int64_t argmax;
-    int32_t n_nonfinite;
-    int32_t n_negc2;
     double c_max;
-    double p_ball, a2_ball;        // sums over the sensors' cells
-    int32_t n_ball_p, n_ball_a;    // and their counts
+    double p_ball[2], a2_ball[2];  // sums over the sensors' cells, and their rounding errors
+    uint32_t n_ball_p, n_ball_a;   // and their counts; bit 31: some cell is non-finite / has c^2 <= 0
 };
 
-// One (sample, tile) work item of a batched launch.
+// One (sample, tile) work item of a batched launch.  A launch without a list
+// runs the tiles of sample 0 in order.
 struct WorkItem {
     int32_t sample;
     int32_t tile;      // tile index within the sample: (zc * nty + ty) * ntx + tx

@@ -3,8 +3,12 @@
 // measures the compiled candidates and stores the fastest.
 #pragma once
 
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
 #include <map>
 #include <tuple>
+#include <vector>
 
 namespace ofm {
 
@@ -24,15 +28,61 @@ struct Tuning {
         return c;
     }
 
-    TileChoice choose(int precision, int ndim, int maxn, int /*n_samples*/) const
+    // The tiling where nothing was set: the one with the least estimated time
+    // of a stage launch over all the samples of a run.
+    //
+    // A workgroup takes `z` planes of its tile one after the other, plus `ends`
+    // planes' work at the chunk's two ends (its latency counts less where a CU
+    // holds few workgroups), and a CU holding b of them takes slope * b + base
+    // times as long as one alone, since they hide each other's latency.  So
+    // where the tiles are few, shorter chunks on more CUs finish first; where
+    // they fill the GPU many times over, long chunks save the ends; in
+    // between, the last round's fill decides.
+    // Measured for 4 steps of one sample with WENO5 (us), 16 planes a chunk
+    // against the choice here: float 48^3 1748 -> 377, 64^3 1739 -> 505, 96^3
+    // 1767 -> 1025, 150^3 3939 -> 3106, 200^3 7079 -> 6636, 256^3 the same;
+    // double 48^3 1965 -> 534, 64^3 1976 -> 766, 96^3 2000 -> 1623, 150^3 7042
+    // -> 6235, 200^3 the same.
+    // Tilings give the same results bit for bit, so that a batch's choice can
+    // follow its total without changing any sample's.
+    TileChoice choose(int precision, int ndim, const std::vector<int>& sizes) const
     {
+        const int maxn = *std::max_element(sizes.begin(), sizes.end());
         auto it = table.find(std::make_tuple(precision, ndim, size_class(maxn)));
         if (it != table.end()) return it->second;
+        TileChoice t = general(precision, ndim, maxn);
+        // 1-D, 4 steps with 64 cells a tile against 256 (us): 1024 cells, 214
+        // against 222; 4096, 210 against 219; equal at 64 and 256
+        if (ndim == 1 && maxn > 256) t.tx = 64;
+        if (ndim != 3) return t;
+        const bool dbl = precision == 1;
+        const double slope = dbl ? 0.81 : 0.48, base = dbl ? 0.0 : 0.35, least = dbl ? 1.1 : 1.0;
+        double best = INFINITY;
+        for (int ty : { 14, 16 })
+            for (int z : { 32, 24, 16, 12, 8, 6, 4, 3, 2, 1 }) {
+                const int64_t n_tiles = tiles(sizes, 16, ty, z);
+                if (n_tiles > kMaxTiles) continue;
+                // a plane of a 16 x 16 tile against one of 16 x 14: more cells,
+                // but (in double above all) less of the GPU's latency hidden
+                const double plane = ty == 14 ? 1.0 : dbl ? 1.35 : 1.17;
+                const double b = (double)((n_tiles + kCUs - 1) / kCUs);
+                const double ends = 0.1 + (dbl ? 0.5 : 0.7) * (1.0 - 1.0 / b);
+                const double cost = plane * (z + ends) * std::max(slope * b + base, least);
+                if (cost < best) {
+                    best = cost;
+                    t.ty = ty;
+                    t.zchunk = z;
+                }
+            }
+        return t;
+    }
+
+    // Fewer tiles, for grids beyond kMaxTiles and where the tiles' scratch is
+    // limited.
+    static TileChoice general(int precision, int ndim, int maxn)
+    {
         TileChoice t;
         if (ndim == 3) {
-            // the autotuner's picks on the 500-bubble cloud: float 16 x 16
-            // tiles of 16 planes up to 256^3, double 16 x 14 tiles of 16
-            // planes; both 16 x 14 tiles of 32 planes at 512^3 and above
             t.tx = 16;
             t.ty = precision == 1 || maxn >= 512 ? 14 : 16;
             t.zchunk = maxn >= 512 ? 32 : 16;
@@ -47,6 +97,21 @@ struct Tuning {
         }
         t.graph_steps = maxn >= 256 ? 4 : 16;
         return t;
+    }
+
+    static int64_t tiles(const std::vector<int>& sizes, int tx, int ty, int z)
+    {
+        int64_t k = 0;
+        for (int n : sizes) k += (int64_t)((n + tx - 1) / tx) * ((n + ty - 1) / ty) * ((n + z - 1) / z);
+        return k;
+    }
+
+    static constexpr int kCUs = 256;            // of the GPU
+    static constexpr int64_t kMaxTiles = 32768; // of a default tiling: 2.3 MB of partials
+
+    bool has(int precision, int ndim, int n) const
+    {
+        return table.count(std::make_tuple(precision, ndim, size_class(n))) != 0;
     }
 
     void set(int precision, int ndim, int n, const TileChoice& t)

@@ -152,6 +152,50 @@ def test_fp32_tiling_invariance_bitwise(ctx):
         assert np.array_equal(o, outs[0])
 
 
+# chunks of one plane, of a few, 16 x 16 tiles, a last round partly full, more
+# than 1024 tiles (the finalisation by sixteen wavefronts)
+@pytest.mark.parametrize("precision,ndim,n", [("f32", 3, 20), ("f32", 3, 48), ("f32", 3, 81), ("f32", 3, 130),
+                                              ("f64", 3, 33), ("f64", 3, 64), ("f64", 3, 98), ("f64", 2, 160),
+                                              ("f64", 1, 300)])
+def test_default_tiling_is_bitwise_the_general_one(precision, ndim, n):
+    """Without a tuned entry the tiling follows the size.  State, step sizes
+    and QoI (the sensors' sums carry their rounding errors) are those of large
+    tiles, bit for bit."""
+    from paper_1705_04374_amd import capi
+    say("default tiling", precision, ndim, n)
+    if ndim == 1:
+        cfg = dict(BASE)
+        cfg.update(ndim=1, n=n, eos=dict(EOS))
+        W, bub = riemann_primitives(1, n, dict(a1r1=1000.0, a2r2=0.0, u=0.0, p=1e9, a2=0.0),
+                                    dict(a1r1=0.0, a2r2=50.0, u=0.0, p=1e5, a2=1.0)), None
+    else:
+        W, cfg = None, solver_config("cloud50" if ndim == 3 else "cloud2d", n)
+        bub = sample_cloud(cloud_spec("cloud50" if ndim == 3 else "cloud2d"), MASTER_SEED, 0, 7)
+    tune = {1: (256, 1, 1, 2), 2: (16, 14, 1, 2), 3: (16, 16, 16, 2)}[ndim]
+    a = gpu_run(capi.Context(0), cfg, precision, bubbles=bub, W=W, n_steps=3)
+    b = gpu_run(capi.Context(0), cfg, precision, bubbles=bub, W=W, n_steps=3, tune=tune)
+    assert np.array_equal(a[0], b[0])
+    assert a[1] == b[1]
+    assert np.array_equal(a[2], b[2])
+
+
+@pytest.mark.parametrize("precision", ["f32", "f64"])
+def test_batch_in_3d_equals_single_solves(precision):
+    """The batch's tiling follows its total: each sample's QoI stays what it
+    is alone, bit for bit."""
+    from paper_1705_04374_amd import capi
+    say("3-D batch vs single", precision)
+    ctx = capi.Context(0)
+    specs, bubs = [], []
+    for i, n in enumerate([64, 20, 64, 48, 20, 32]):
+        specs.append(capi.make_spec(solver_config("cloud50", n), precision, n_steps=4 + i))
+        bubs.append(sample_cloud(cloud_spec("cloud50"), MASTER_SEED, 3, i))
+    qb = capi.ofm_solve_batch(ctx, specs, bubs)
+    for s, b, q in zip(specs, bubs, qb):
+        assert capi.ofm_solve(ctx, s, b) == q
+    ctx.close()
+
+
 def test_autotune_times_every_candidate_and_keeps_the_fastest(ctx):
     import torch
     from paper_1705_04374_amd import capi
