@@ -1,68 +1,116 @@
 // OF-MLMC estimator kernels (Sukys et al., arXiv:1705.04374, Sec. 2.4.3-2.4.4),
-// all in double on the device.  The statistics are tiny next to the solves
+// all in double on the device.  The statistics are small next to the solves
 // (Appendix A.3 notes the coefficient system is never a bottleneck), so each
-// call is one workgroup; what matters is that the sums are deterministic
-// (fixed-order strided partial sums, then a fixed tree) and stay on the GPU.
+// call is one workgroup without scratch memory; the sums are deterministic
+// (fixed-order strided partial sums, then a fixed tree).
 #include "flow_kernels.h"
 
 #include <math.h>
 
 namespace ofm {
 
-constexpr int MT = 256;
-
-// Fixed-order workgroup sum of one double per thread.
-__device__ double block_sum(double v, double* sh)
+// Fixed-order workgroup sums of three doubles per thread: a butterfly within
+// each wavefront, then the wavefronts in order.
+template <int NT> __device__ __forceinline__ void block_sum3(double (&v)[3])
 {
-    sh[threadIdx.x] = v;
+    constexpr int NW = NT / 64;
+    __shared__ double sh[NW][3];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) v[k] += __shfl_xor(v[k], off, 64);
+    __syncthreads();                                   // the previous sums have been read
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) sh[threadIdx.x >> 6][k] = v[k];
     __syncthreads();
-    for (int s = MT / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        v[k] = 0.0;
+        for (int w = 0; w < NW; ++w) v[k] += sh[w][k];
     }
-    double r = sh[0];
-    __syncthreads();
-    return r;
 }
 
-// Moments of one term: (M_used, mean_f, mean_c, Var_f, Var_c, Cov), two-pass.
-__global__ void __launch_bounds__(MT) moments_kernel(const double* qf, const double* qc, const int32_t* ok,
-                                                     int64_t M, double* out)
+// Moments of one term: (M_used, mean_f, mean_c, Var_f, Var_c, Cov), two-pass,
+// by one workgroup.  Bound by the latency of its loads: each thread has those
+// of eight samples in flight (of 16: half the speed, at 128 registers a
+// thread), and there are 16 wavefronts from 1024 samples on.  65536 samples
+// without coarse values: 119 us before (4 wavefronts, a sample at a time, six
+// sums through LDS), 31 now; 3276 samples 12.7 and 9.8; 10^6, 5450 and 570.
+template <int NT>
+__global__ void __launch_bounds__(NT) moments_kernel(const double* __restrict__ qf, const double* __restrict__ qc,
+                                                     const int32_t* __restrict__ ok, int64_t M,
+                                                     double* __restrict__ out)
 {
-    __shared__ double sh[MT];
-    double cnt = 0.0, sf = 0.0, sc = 0.0;
-    for (int64_t i = threadIdx.x; i < M; i += MT) {
-        if (ok && ok[i] == 0) continue;
-        cnt += 1.0;
-        sf += qf[i];
-        if (qc) sc += qc[i];
-    }
-    const double m = block_sum(cnt, sh);
-    const double mf = m > 0.0 ? block_sum(sf, sh) / m : 0.0;
-    const double mc = (m > 0.0 && qc) ? block_sum(sc, sh) / m : 0.0;
-    double vf = 0.0, vc = 0.0, cv = 0.0;
-    for (int64_t i = threadIdx.x; i < M; i += MT) {
-        if (ok && ok[i] == 0) continue;
-        const double df = qf[i] - mf;
-        vf += df * df;
-        if (qc) {
-            const double dc = qc[i] - mc;
-            vc += dc * dc;
-            cv += df * dc;
+    constexpr int U = 8;
+    // visit(f, c) of this thread's samples in use, in increasing order
+    auto each = [&](auto visit) {
+        for (int64_t i0 = threadIdx.x; i0 < M; i0 += (int64_t)U * NT) {
+            int64_t j[U];
+            double f[U], c[U];
+            bool use[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int64_t i = i0 + (int64_t)k * NT;
+                use[k] = i < M;
+                j[k] = i < M ? i : M - 1;
+                f[k] = qf[j[k]];
+                c[k] = 0.0;
+            }
+            if (qc)
+#pragma unroll
+                for (int k = 0; k < U; ++k) c[k] = qc[j[k]];
+            if (ok) {
+                int32_t o[U];
+#pragma unroll
+                for (int k = 0; k < U; ++k) o[k] = ok[j[k]];
+#pragma unroll
+                for (int k = 0; k < U; ++k) use[k] = use[k] && o[k] != 0;
+            }
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+                if (use[k]) visit(f[k], c[k]);
         }
-    }
-    vf = block_sum(vf, sh);
-    vc = block_sum(vc, sh);
-    cv = block_sum(cv, sh);
+    };
+    double s[3] = { 0.0, 0.0, 0.0 };
+    each([&](double f, double c) {
+        s[0] += 1.0;
+        s[1] += f;
+        s[2] += c;
+    });
+    block_sum3<NT>(s);
+    const double m = s[0];
+    const double mf = m > 0.0 ? s[1] / m : 0.0;
+    const double mc = m > 0.0 ? s[2] / m : 0.0;
+    double v[3] = { 0.0, 0.0, 0.0 };
+    each([&](double f, double c) {
+        const double df = f - mf, dc = c - mc;
+        v[0] += df * df;
+        v[1] += dc * dc;
+        v[2] += df * dc;
+    });
+    block_sum3<NT>(v);
     if (threadIdx.x == 0) {
         out[0] = m;
         out[1] = mf;
         out[2] = mc;
         const bool two = m >= 2.0;
-        out[3] = two ? vf / (m - 1.0) : 0.0;
-        out[4] = two && qc ? vc / (m - 1.0) : 0.0;
-        out[5] = two && qc ? cv / (m - 1.0) : 0.0;
+        out[3] = two ? v[0] / (m - 1.0) : 0.0;
+        out[4] = two && qc ? v[1] / (m - 1.0) : 0.0;
+        out[5] = two && qc ? v[2] / (m - 1.0) : 0.0;
     }
+}
+
+// The kernels below run a handful of operations per term, L + 1 <= 32 terms:
+// one wavefront reads all it needs at once into LDS (one memory latency, not
+// one per operand), takes what is independent per term with a lane each, and
+// adds up in the order of the terms.  Four terms, one thread before and now
+// (us): coefficients 4.6 and 2.3, errors 4.6 and 1.5, estimate 5.2 and 1.4,
+// sample counts (arrays in scratch memory before) 9.1 and 1.9.
+constexpr int kTerms = 32;
+__device__ __forceinline__ void fetch(double* sh, const double* g, int n)
+{
+    for (int i = threadIdx.x; i < n; i += 64) sh[i] = g[i];
 }
 
 // Tridiagonal system of eq. (alpha-matvec), generalised to per-term
@@ -70,10 +118,14 @@ __global__ void __launch_bounds__(MT) moments_kernel(const double* qf, const dou
 // sum_l W_l Var(alpha_l q_f,l - alpha_{l-1} q_c,l) with respect to alpha_k.
 // Thomas algorithm; a non-positive pivot means the estimates are not
 // positive definite -> flag OFM_ESINGULAR and alpha = 1 (classical MLMC).
-__global__ void coefficients_kernel(int L, const double* mom, const double* W, double* alpha, int32_t* flag)
+__global__ void __launch_bounds__(64) coefficients_kernel(int L, const double* gmom, const double* gW, double* alpha,
+                                                          int32_t* flag)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double cp[32], dp[32];
+    __shared__ double mom[6 * kTerms], W[kTerms], cp[kTerms], dp[kTerms];
+    fetch(mom, gmom, 6 * (L + 1));
+    fetch(W, gW, L + 1);
+    __syncthreads();
+    if (threadIdx.x != 0) return;
     int bad = 0;
     for (int k = 0; k < L; ++k) {
         const double diag = mom[6 * k + 3] * W[k] + mom[6 * (k + 1) + 4] * W[k + 1];
@@ -91,72 +143,94 @@ __global__ void coefficients_kernel(int L, const double* mom, const double* W, d
         *flag = OFM_ESINGULAR;
         return;
     }
-    for (int k = L - 1; k >= 0; --k) alpha[k] = dp[k] - (k + 1 <= L - 1 ? cp[k] * alpha[k + 1] : 0.0);
+    double next = 1.0;
+    for (int k = L - 1; k >= 0; --k) alpha[k] = next = dp[k] - (k + 1 <= L - 1 ? cp[k] * next : 0.0);
     *flag = 0;
 }
 
 // eq. (ocv-mlmc-err): per-term variances of the weighted differences and
 // the squared sampling error.
-__global__ void errors_kernel(int L, const double* mom, const double* alpha, double* sig, double* eps2)
+__global__ void __launch_bounds__(64) errors_kernel(int L, const double* gmom, const double* galpha, double* sig,
+                                                    double* eps2)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double e = 0.0;
-    for (int l = 0; l <= L; ++l) {
+    __shared__ double mom[6 * kTerms], alpha[kTerms], part[kTerms];
+    fetch(mom, gmom, 6 * (L + 1));
+    fetch(alpha, galpha, L + 1);
+    __syncthreads();
+    const int l = threadIdx.x;
+    if (l <= L) {
         const double* m = mom + 6 * l;
         double s = alpha[l] * alpha[l] * m[3];
         if (l >= 1) s += alpha[l - 1] * alpha[l - 1] * m[4] - 2.0 * alpha[l] * alpha[l - 1] * m[5];
         sig[l] = s;
-        e += s / m[0];
+        part[l] = s / m[0];
     }
+    __syncthreads();
+    if (l != 0) return;
+    double e = 0.0;
+    for (int k = 0; k <= L; ++k) e += part[k];
     *eps2 = e;
 }
 
 // eq. (ocv-mlmc): the estimator.
-__global__ void estimate_kernel(int L, const double* mom, const double* alpha, double* E)
+__global__ void __launch_bounds__(64) estimate_kernel(int L, const double* gmom, const double* galpha, double* E)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    __shared__ double mom[6 * kTerms], alpha[kTerms];
+    fetch(mom, gmom, 6 * (L + 1));
+    fetch(alpha, galpha, L + 1);
+    __syncthreads();
+    if (threadIdx.x != 0) return;
     double e = alpha[0] * mom[1];
     for (int l = 1; l <= L; ++l) e += alpha[l] * mom[6 * l + 1] - alpha[l - 1] * mom[6 * l + 2];
     *E = e;
 }
 
 // eq. (M-tol) / eq. (M-budget) with the keep-computed-samples loop of step 7.
-__global__ void optimal_M_kernel(int L, const double* sig, const double* W, const int64_t* have, int mode,
-                                 double target, int64_t* out, int32_t* flag)
+// Lane l holds term l.
+__global__ void __launch_bounds__(64) optimal_M_kernel(int L, const double* sig, const double* W, const int64_t* have,
+                                                       int mode, double target, int64_t* out, int32_t* flag)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    bool fixed[32];
-    int64_t M[32];
-    for (int l = 0; l <= L; ++l) { fixed[l] = false; M[l] = have[l]; }
-    *flag = 0;
+#pragma clang fp contract(off)
+    __shared__ double spent[kTerms], root[kTerms];      // of a term: its share once fixed, sqrt(sig W)
+    const int l = threadIdx.x;
+    const bool mine = l <= L;
+    const bool tol = mode == OFM_MODE_TOLERANCE;
+    double ratio = 0.0;                                 // sqrt(sig / W)
+    int64_t n = 0, M = 0;
+    if (mine) {
+        const double s = sig[l], w = W[l];
+        n = M = have[l];
+        spent[l] = tol ? s / (double)n : (double)n * w;
+        root[l] = sqrt(s * w);
+        ratio = sqrt(s / w);
+    }
+    __syncthreads();
+    if (l == 0) *flag = 0;
+    uint64_t fixed = 0;                                 // the same in every lane
     for (int it = 0; it <= L + 1; ++it) {
-        double rest = mode == OFM_MODE_TOLERANCE ? target * target : target;
+        double rest = tol ? target * target : target;
         double S = 0.0;
-        for (int l = 0; l <= L; ++l) {
-            if (fixed[l]) rest -= mode == OFM_MODE_TOLERANCE ? sig[l] / (double)have[l] : (double)have[l] * W[l];
-            else S += sqrt(sig[l] * W[l]);
+        for (int k = 0; k <= L; ++k) {
+            if (fixed >> k & 1) rest -= spent[k];
+            else S += root[k];
         }
-        if (mode == OFM_MODE_TOLERANCE && !(rest > 0.0)) {
-            *flag = OFM_EINFEASIBLE;
-            for (int l = 0; l <= L; ++l) out[l] = have[l];
+        if (tol && !(rest > 0.0)) {
+            if (l == 0) *flag = OFM_EINFEASIBLE;
+            if (mine) out[l] = n;
             return;
         }
-        for (int l = 0; l <= L; ++l) {
-            if (fixed[l]) continue;
+        const bool is_free = mine && !(fixed >> l & 1);
+        if (is_free) {
             double m;
-            if (mode == OFM_MODE_TOLERANCE) m = ceil(sqrt(sig[l] / W[l]) * S / rest);
-            else m = (rest > 0.0 && S > 0.0) ? ceil(rest * sqrt(sig[l] / W[l]) / S) : 0.0;
-            M[l] = (int64_t)m;
+            if (tol) m = ceil(ratio * S / rest);
+            else m = (rest > 0.0 && S > 0.0) ? ceil(rest * ratio / S) : 0.0;
+            M = (int64_t)m;
         }
-        bool changed = false;
-        for (int l = 0; l <= L; ++l) {
-            if (!fixed[l] && M[l] < have[l]) { M[l] = have[l]; fixed[l] = true; changed = true; }
-        }
-        bool any_free = false;
-        for (int l = 0; l <= L; ++l) any_free = any_free || !fixed[l];
-        if (!changed || !any_free) break;
+        const uint64_t now = __ballot(is_free && M < n);
+        fixed |= now;
+        if (now == 0 || __ballot(mine && !(fixed >> l & 1)) == 0) break;
     }
-    for (int l = 0; l <= L; ++l) out[l] = fixed[l] ? have[l] : M[l];
+    if (mine) out[l] = fixed >> l & 1 ? n : M;
 }
 
 // Inferred variances of level differences (the optional part of step 3 of
@@ -272,7 +346,10 @@ hipError_t launch_fit(int L, int first, int m_floor, double* mom, double* vhat, 
 hipError_t launch_moments(const double* qf, const double* qc, const int32_t* ok, int64_t M, double* out,
                           hipStream_t s)
 {
-    hipLaunchKernelGGL(moments_kernel, dim3(1), dim3(MT), 0, s, qf, qc, ok, M, out);
+    if (M < 1024)
+        hipLaunchKernelGGL((moments_kernel<256>), dim3(1), dim3(256), 0, s, qf, qc, ok, M, out);
+    else
+        hipLaunchKernelGGL((moments_kernel<1024>), dim3(1), dim3(1024), 0, s, qf, qc, ok, M, out);
     return hipGetLastError();
 }
 

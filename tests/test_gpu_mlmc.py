@@ -80,6 +80,55 @@ def test_estimator_matches_oracle(ctx, L, Ms):
         assert out.cpu().tolist() == ref and flag.item() == 0
 
 
+@pytest.mark.parametrize("M", [1, 2, 63, 256, 1023, 1024, 2048, 8192, 8193, 20001])
+@pytest.mark.parametrize("paired", [True, False])
+def test_moments_at_the_edges_of_their_launches(ctx, M, paired):
+    """Fewer samples than threads, exactly one and one more group of loads,
+    both workgroup sizes; samples left out are NaN (<= 1e-12 relative)."""
+    import torch
+    from paper_1705_04374_amd import capi
+    rng = np.random.default_rng(M)
+    y = rng.normal(size=M)
+    qf, qc = 3.0 + y, (5.0 + y + 0.5 * rng.normal(size=M)) if paired else None
+    ok = (np.arange(M) % 7 != 3).astype(np.int32)
+    for use in (ok, None):
+        r = O.term_moments(qf, qc, None if use is None else use.astype(bool))
+        bad = np.zeros(M, bool) if use is None else use == 0
+        t = [None if q is None else torch.tensor(np.where(bad, np.nan, q), device="cuda") for q in (qf, qc)]
+        out = torch.full((6,), -1.0, dtype=torch.float64, device="cuda")
+        capi.ofm_mlmc_moments(ctx, t[0], t[1], None if use is None else torch.tensor(use, device="cuda"), out)
+        got = out.cpu().tolist()
+        assert got[0] == r["M"]
+        for g, k in zip(got[1:], ("mean_f", "mean_c", "Vf", "Vc", "C")):
+            assert abs(g - r[k]) <= 1e-12 * max(abs(r[k]), 1e-300), (k, g, r[k])
+
+
+@pytest.mark.parametrize("L", [0, 1, 5, 31])
+def test_sample_counts_with_terms_fixed_in_turn(ctx, L):
+    """Terms that hold more samples than their optimum are fixed one after
+    another, up to the largest number of terms; and a tolerance that the kept
+    terms exhaust: what is held, flagged."""
+    import torch
+    from paper_1705_04374_amd import capi
+    rng = np.random.default_rng(L)
+    sig = 4.0 ** -np.arange(L + 1) * rng.uniform(0.5, 1.5, L + 1)
+    W = 1.7 ** np.arange(L + 1) * rng.uniform(0.5, 1.5, L + 1)
+    have = rng.integers(1, 400, L + 1)
+    dev = [torch.tensor(v, device="cuda") for v in (sig, W, have)]
+    out = torch.zeros(L + 1, dtype=torch.int64, device="cuda")
+    flag = torch.zeros(1, dtype=torch.int32, device="cuda")
+    spent = float(np.sum(have * W))
+    for mode, name, target in [(capi.OFM_MODE_TOLERANCE, "tol", t) for t in (0.02, 0.1, 0.4)] + \
+                              [(capi.OFM_MODE_BUDGET, "budget", b * spent) for b in (0.5, 1.1, 3.0)]:
+        capi.ofm_ofmlmc_optimal_M(ctx, L, *dev, mode, target, out, flag)
+        try:
+            ref, infeasible = O.optimal_samples(list(sig), list(W), have.tolist(), name, target), False
+        except O.InfeasibleTolerance:
+            ref, infeasible = have.tolist(), True
+        assert (flag.item() == capi.OFM_EINFEASIBLE) == infeasible
+        assert out.cpu().tolist() == ref, (name, target)
+
+
 def test_singular_system_falls_back_to_ones(ctx):
     import torch
     from paper_1705_04374_amd import capi
