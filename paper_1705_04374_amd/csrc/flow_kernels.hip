@@ -706,7 +706,7 @@ constexpr int round_up64(int x) { return (x + 63) / 64 * 64; }
 
 // Threads per workgroup of a TX x TY tile: the cell count rounded up to whole
 // wavefronts (threads past the last cell help with the x-y tasks only).
-template <int TX, int TY> constexpr int stage_threads() { return round_up64(TX * TY); }
+template <int TX, int TY> constexpr int cell_threads() { return round_up64(TX * TY); }
 
 // How a stage kernel is laid out, by type, RK stage and WENO order.
 //   split  the x-y part of a plane split by axis (the x edges, x faces and x
@@ -737,23 +737,39 @@ struct StageLayout {
     int waves;
     bool early, late;
 };
-template <typename T, int ND, int STAGE, int ORD> constexpr StageLayout stage_layout()
+template <typename T, int ND, int TY, int STAGE, int ORD> constexpr StageLayout stage_layout()
 {
+    if (ND == 2 && sizeof(T) == 8 && TY <= 8) return { false, 2, false, false };   // for small grids: both axes at once
     if (sizeof(T) == 8) return { true, 2, STAGE < 2, false };
     if (ND < 3) return { false, 3, false, false };
     if (ORD == 3) return { true, 4, false, false };
     return STAGE < 2 ? StageLayout{ false, 3, true, true } : StageLayout{ false, 4, false, false };
 }
 
+// Threads of the stage kernel.  Below three dimensions a launch is one plane
+// of work, mostly latency: a thread for each edge and each face, so that none
+// takes two in turn (split: for each of an axis).  4 steps with a thread per
+// cell and now (us): float 64^2 222 and 209 (16 x 14 tiles), 1024^2 687 and
+// 677; double 64^2 in 16 x 8 tiles 286 and 218; 1-D, 1000 cells 215 and 197.
+template <typename T, int ND, int TX, int TY> constexpr int stage_threads()
+{
+    constexpr int ex = TY * (TX + 2), ey = ND == 2 ? (TY + 2) * TX : 0;
+    constexpr int fx = TY * (TX + 1), fy = ND == 2 ? (TY + 1) * TX : 0;
+    if (ND == 3) return cell_threads<TX, TY>();
+    if (ND == 1) return round_up64(ex);
+    if (stage_layout<T, ND, TY, 0, 5>().split) return round_up64(ex > ey ? ex : ey);
+    return round_up64(ex + ey > round_up64(fx) + fy ? ex + ey : round_up64(fx) + fy);
+}
+
 // RK stage STAGE = 0, 1, 2 (compiled separately: only the last carries the
 // reduction, only the first skips dU); WENO order ORD = 5 or 3.
 template <typename T, int ND, int TX, int TY, int STAGE, int ORD>
-__global__ void __launch_bounds__((stage_threads<TX, TY>()))
-__attribute__((amdgpu_waves_per_eu(stage_layout<T, ND, STAGE, ORD>().waves)))
+__global__ void __launch_bounds__((stage_threads<T, ND, TX, TY>()))
+__attribute__((amdgpu_waves_per_eu(stage_layout<T, ND, TY, STAGE, ORD>().waves)))
 stage_kernel(LaunchArgs a)
 {
     constexpr int NV = 4 + ND;
-    constexpr int NT = stage_threads<TX, TY>();
+    constexpr int NT = stage_threads<T, ND, TX, TY>();
     constexpr int HX = TX + 6;
     constexpr int HY = ND >= 2 ? TY + 6 : 1;
     // Task lists of the x-y phases.  Edge tasks: x then y, contiguous (a
@@ -773,8 +789,8 @@ stage_kernel(LaunchArgs a)
     constexpr int AL = WSZ > FSZ ? WSZ : FSZ;          // W plane and face fluxes share LDS
     // split pass: edge tasks of one axis at a time; an axis's face fluxes
     // ((NV+1) x its faces <= 2 NV x its edge tasks) overwrite its edges
-    constexpr bool SPLIT = stage_layout<T, ND, STAGE, ORD>().split;
-    constexpr bool EARLY = stage_layout<T, ND, STAGE, ORD>().early, LATE = stage_layout<T, ND, STAGE, ORD>().late;
+    constexpr bool SPLIT = stage_layout<T, ND, TY, STAGE, ORD>().split;
+    constexpr bool EARLY = stage_layout<T, ND, TY, STAGE, ORD>().early, LATE = stage_layout<T, ND, TY, STAGE, ORD>().late;
     constexpr int ESX = EXN > EYN ? EXN : EYN;
     constexpr int EST = SPLIT ? ESX : ES;              // stride of the edge arrays
     static_assert(!SPLIT || ((NV + 1) * FXN <= 2 * NV * ESX && (NV + 1) * FYN <= 2 * NV * ESX), "face alias");
@@ -1144,10 +1160,10 @@ stage_kernel(LaunchArgs a)
 // Reduction of a state without stepping (initial level)
 // ---------------------------------------------------------------------------
 template <typename T, int ND, int TX, int TY>
-__global__ void __launch_bounds__((stage_threads<TX, TY>())) reduce_kernel(LaunchArgs a)
+__global__ void __launch_bounds__((cell_threads<TX, TY>())) reduce_kernel(LaunchArgs a)
 {
     constexpr int NV = 4 + ND;
-    constexpr int NT = stage_threads<TX, TY>();
+    constexpr int NT = cell_threads<TX, TY>();
     const int wi = xcd_swizzle(blockIdx.x, gridDim.x);
     if (wi >= a.n_work) return;
     const WorkItem item = a.work ? a.work[wi] : WorkItem{ 0, wi };
@@ -1399,7 +1415,7 @@ __global__ void __launch_bounds__(256) to_conserved_kernel(PhysD ph, const T* u,
 template <typename T, int ND, int TX, int TY>
 static hipError_t launch_stage_t(const LaunchArgs& a, int stage, hipStream_t s)
 {
-    const dim3 grid(a.n_work), block(stage_threads<TX, TY>());
+    const dim3 grid(a.n_work), block(stage_threads<T, ND, TX, TY>());
     if (a.ph.order == 3) {
         if (stage == 0) hipLaunchKernelGGL((stage_kernel<T, ND, TX, TY, 0, 3>), grid, block, 0, s, a);
         else if (stage == 1) hipLaunchKernelGGL((stage_kernel<T, ND, TX, TY, 1, 3>), grid, block, 0, s, a);
@@ -1417,7 +1433,7 @@ static hipError_t launch_stage_t(const LaunchArgs& a, int stage, hipStream_t s)
 template <typename T, int ND, int TX, int TY>
 static hipError_t launch_reduce_t(const LaunchArgs& a, hipStream_t s)
 {
-    hipLaunchKernelGGL((reduce_kernel<T, ND, TX, TY>), dim3(a.n_work), dim3(stage_threads<TX, TY>()), 0, s, a);
+    hipLaunchKernelGGL((reduce_kernel<T, ND, TX, TY>), dim3(a.n_work), dim3(cell_threads<TX, TY>()), 0, s, a);
     return hipGetLastError();
 }
 
@@ -1465,7 +1481,7 @@ static int stage_blocks_per_cu_t(int order)
     int b = 0;
     const void* f = order == 3 ? reinterpret_cast<const void*>(&stage_kernel<T, ND, TX, TY, 2, 3>)
                                : reinterpret_cast<const void*>(&stage_kernel<T, ND, TX, TY, 2, 5>);
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, f, stage_threads<TX, TY>(), 0) != hipSuccess) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, f, stage_threads<T, ND, TX, TY>(), 0) != hipSuccess) {
         (void)hipGetLastError();
         return 0;
     }

@@ -51,11 +51,28 @@ struct Tuning {
         auto it = table.find(std::make_tuple(precision, ndim, size_class(maxn)));
         if (it != table.end()) return it->second;
         TileChoice t = general(precision, ndim, maxn);
-        // 1-D, 4 steps with 64 cells a tile against 256 (us): 1024 cells, 214
-        // against 222; 4096, 210 against 219; equal at 64 and 256
-        if (ndim == 1 && maxn > 256) t.tx = 64;
-        if (ndim != 3) return t;
         const bool dbl = precision == 1;
+        if (ndim == 1) {
+            // 4 steps with 64 cells a tile against 256 (us): 64 cells 188
+            // against 197, 256 194 and 204, 4000 189 and 196
+            t.tx = 64;
+            return t;
+        }
+        if (ndim == 2) {
+            // double: 16 x 8 tiles up to two a CU, whose workgroups take both
+            // axes at once, then 16 x 14, which redo less of their halos
+            // (4 steps, us: 64^2 218 against 233, 256^2 255 and 285, 320^2
+            // 345 and 291).  float: 16 x 16 where that saves a second tile a
+            // CU (256^2 218 against 236; 160^2 216 and 211, 320^2 252 and 237).
+            const auto tiles2 = [&](int ty) {
+                int64_t k = 0;
+                for (int n : sizes) k += (int64_t)((n + 15) / 16) * ((n + ty - 1) / ty);
+                return k;
+            };
+            if (dbl) t.ty = tiles2(8) <= 2 * kCUs ? 8 : 14;
+            else t.ty = tiles2(16) <= kCUs && tiles2(14) > kCUs ? 16 : 14;
+            return t;
+        }
         const double slope = dbl ? 0.81 : 0.48, base = dbl ? 0.0 : 0.35, least = dbl ? 1.1 : 1.0;
         double best = INFINITY;
         for (int ty : { 14, 16 })

@@ -155,8 +155,9 @@ def test_fp32_tiling_invariance_bitwise(ctx):
 # chunks of one plane, of a few, 16 x 16 tiles, a last round partly full, more
 # than 1024 tiles (the finalisation by sixteen wavefronts)
 @pytest.mark.parametrize("precision,ndim,n", [("f32", 3, 20), ("f32", 3, 48), ("f32", 3, 81), ("f32", 3, 130),
-                                              ("f64", 3, 33), ("f64", 3, 64), ("f64", 3, 98), ("f64", 2, 160),
-                                              ("f64", 1, 300)])
+                                              ("f64", 3, 33), ("f64", 3, 64), ("f64", 3, 98), ("f64", 2, 29),
+                                              ("f64", 2, 160), ("f64", 2, 300), ("f32", 2, 45), ("f32", 2, 255),
+                                              ("f64", 1, 64), ("f64", 1, 300), ("f32", 1, 65)])
 def test_default_tiling_is_bitwise_the_general_one(precision, ndim, n):
     """Without a tuned entry the tiling follows the size.  State, step sizes
     and QoI (the sensors' sums carry their rounding errors) are those of large
