@@ -373,19 +373,21 @@ static int run_begin(ofm_ctx* ctx, ofm_run& r, bool init, int64_t dts_len, hipSt
     HIPCHK(ctx, hipEventRecord(e0, stream));
 
     const PhysD ph = make_phys(s0);
+    std::vector<char> clouds;           // until the copy is done, below
     if (init) {
+        // the bubbles of all members, then the members' clouds
         size_t nbub = 0;
         for (const Member& m : mem) nbub += (size_t)m.nb;
-        int rc = grow(ctx, &ctx->bub, &ctx->bub_bytes, sizeof(double) * 4 * std::max<size_t>(nbub, 1));
+        const size_t o_list = align256(sizeof(double) * 4 * nbub);
+        clouds.resize(o_list + sizeof(InitLaunch) * ns);
+        int rc = grow(ctx, &ctx->bub, &ctx->bub_bytes, clouds.size());
         if (rc) return rc;
-        std::vector<double> hb;
-        hb.reserve(4 * nbub);
-        for (const Member& m : mem) hb.insert(hb.end(), m.bubbles, m.bubbles + 4 * (size_t)m.nb);
-        if (nbub)
-            HIPCHK(ctx, hipMemcpyAsync(ctx->bub, hb.data(), sizeof(double) * hb.size(), hipMemcpyHostToDevice, stream));
+        InitLaunch* list = (InitLaunch*)(clouds.data() + o_list);
         size_t off = 0;
-        for (const Member& m : mem) {
-            InitLaunch L;
+        for (int i = 0; i < ns; ++i) {
+            const Member& m = mem[i];
+            if (m.nb) memcpy(clouds.data() + sizeof(double) * 4 * off, m.bubbles, sizeof(double) * 4 * (size_t)m.nb);
+            InitLaunch& L = list[i];
             L.ph = ph;
             L.bubbles = (const double*)ctx->bub + 4 * off;
             L.nb = m.nb;
@@ -396,11 +398,23 @@ static int run_begin(ofm_ctx* ctx, ofm_run& r, bool init, int64_t dts_len, hipSt
             for (int a = 0; a < 3; ++a) L.center[a] = m.spec.center[a];
             L.radius = m.spec.cloud_radius; L.delta = m.spec.ramp_delta; L.width = m.spec.ramp_width;
             L.u = m.buf0;
-            HIPCHK(ctx, launch_init(prec, nd, L, stream));
+            // a launch takes up to 2^23 workgroups (2^31 threads), or one cloud
+            const int64_t before = i ? (int64_t)list[i - 1].first + init_workgroups(nd, list[i - 1].n) : 0;
+            L.first = before + init_workgroups(nd, L.n) <= 1 << 23 ? (int)before : 0;
             off += (size_t)m.nb;
         }
-        // the host bubbles vector must outlive the copy
-        HIPCHK(ctx, hipStreamSynchronize(stream));
+        HIPCHK(ctx, hipMemcpyAsync(ctx->bub, clouds.data(), clouds.size(), hipMemcpyHostToDevice, stream));
+        const InitLaunch* d_list = (const InitLaunch*)((const char*)ctx->bub + o_list);
+        if (ns == 1)
+            HIPCHK(ctx, launch_init(prec, nd, list[0], stream));
+        else
+            for (int at = 0; at < ns;) {
+                int k = at + 1;
+                while (k < ns && list[k].first > 0) ++k;
+                const int groups = list[k - 1].first + init_workgroups(nd, list[k - 1].n);
+                HIPCHK(ctx, launch_init_batch(prec, nd, d_list + at, k - at, groups, stream));
+                at = k;
+            }
     }
     LaunchArgs& la = r.la;
     la.ph = ph;
@@ -675,7 +689,7 @@ int ofm_state_init(ofm_ctx* ctx, const ofm_solve_spec* spec, const double* bubbl
     rc = grow(ctx, &ctx->bub, &ctx->bub_bytes, sizeof(double) * 4 * std::max(nb, 1));
     if (rc) return rc;
     if (nb) HIPCHK(ctx, hipMemcpyAsync(ctx->bub, bubbles, sizeof(double) * 4 * nb, hipMemcpyHostToDevice, s));
-    InitLaunch L;
+    InitLaunch L{};
     L.ph = make_phys(*spec);
     L.bubbles = (const double*)ctx->bub;
     L.nb = nb;

@@ -14,6 +14,7 @@ struct InitLaunch {
     double center[3];
     double radius, delta, width;
     void* u;                 // [dev] output state
+    int32_t first;           // of a batch's launch: its first workgroup
 };
 
 bool tile_supported(int precision, int ndim, int tx, int ty);
@@ -28,6 +29,9 @@ hipError_t launch_reduce(int precision, int ndim, int tx, int ty, const LaunchAr
 hipError_t launch_finalize(const SampleDesc* desc, SampleState* state, const TilePartial* part, int n_samples,
                            int most_tiles, int initial, double* dt_log, int64_t dt_log_len, hipStream_t s);
 hipError_t launch_init(int precision, int ndim, const InitLaunch& L, hipStream_t s);
+int init_workgroups(int ndim, int n);
+// list: [dev] count clouds, `first` the workgroups of those before it
+hipError_t launch_init_batch(int precision, int ndim, const InitLaunch* list, int count, int workgroups, hipStream_t s);
 hipError_t launch_to_conserved(int precision, int ndim, const PhysD& ph, const void* u, double* q, int64_t ncell,
                                hipStream_t s);
 hipError_t launch_prim_to_cons(int precision, int ndim, const PhysD& ph, const void* w, void* u, int64_t ncell,

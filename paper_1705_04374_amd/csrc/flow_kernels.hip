@@ -729,8 +729,9 @@ template <int TX, int TY> constexpr int cell_threads() { return round_up64(TX * 
 //   float WENO3, 150^3: less work between barriers and fewer registers, so a
 //     fourth wavefront pays: 200, 216, 236 (joint at 3: 225, 256, 279).
 //   double, 192^3: LDS for two axes' edges would halve the occupancy; where
-//     it fits 256 registers, the cell's own loads go ahead: 881, 918, 994
-//     (none early: 910, 944, 994; late: 889, 932, 1098; both: 904, 1022,
+//     it fits 256 registers, the cell's own loads go ahead: 881, 918, 1003
+//     (the third 975 before its sums carried their errors; none early: 910,
+//     944, 1003; early there too 1075; late: 889, 932, 1098; both: 904, 1022,
 //     1223; three waves spill: 1400, 1610, 1853).
 struct StageLayout {
     bool split;
@@ -1260,24 +1261,20 @@ __global__ void __launch_bounds__(NT) finalize_kernel(const SampleDesc* desc, Sa
 }
 
 // ---------------------------------------------------------------------------
-// Initial state of a cloud (one sample per launch)
+// Initial state of a cloud
 // ---------------------------------------------------------------------------
-struct InitArgs {
-    PhysD ph;
-    const double* bubbles;   // nb x 4
-    int32_t nb;
-    int32_t n, n_sub;
-    double rho1, rho2, p_bubble, p_inf;
-    double cx, cy, cz, radius, delta, width;
-    void* u;
-};
+template <int ND> __host__ __device__ constexpr int init_blocks(int n)
+{
+    if (ND == 3) return ((n + 7) / 8) * ((n + 7) / 8) * ((n + 3) / 4);
+    if (ND == 2) return ((n + 15) / 16) * ((n + 15) / 16);
+    return (n + 255) / 256;
+}
 
 // Workgroup = 256 cells (8x8x4 in 3-D, 16x16 in 2-D, 256 in 1-D).  The
 // bubbles are culled against the workgroup's box in chunks of 256 through
 // LDS; each thread keeps a bit mask of its sub-samples found inside.  Inside
 // tests are in double without contraction, as |x - c|^2 < r^2.
-template <typename T, int ND>
-__global__ void __launch_bounds__(256) init_kernel(InitArgs a)
+template <typename T, int ND> __device__ __forceinline__ void init_block(const InitLaunch& a, const int b)
 {
 #pragma clang fp contract(off)
     constexpr int BX = ND == 3 ? 8 : (ND == 2 ? 16 : 256);
@@ -1285,7 +1282,6 @@ __global__ void __launch_bounds__(256) init_kernel(InitArgs a)
     constexpr int BZ = ND == 3 ? 4 : 1;
     const int n = a.n;
     const int nbx = (n + BX - 1) / BX, nby = ND >= 2 ? (n + BY - 1) / BY : 1;
-    const int b = blockIdx.x;
     const int bx = b % nbx, by = (b / nbx) % nby, bz = b / (nbx * nby);
     const int tid = threadIdx.x;
     const int i = bx * BX + tid % BX;
@@ -1349,10 +1345,10 @@ __global__ void __launch_bounds__(256) init_kernel(InitArgs a)
     if (!(i < n && j < (ND >= 2 ? n : 1) && k < (ND == 3 ? n : 1))) return;
     const int ntot = ns * nsy * nsz;
     const double a2 = (double)__popcll(mask) / (double)ntot;
-    double ccx = ((double)i + 0.5) / N - a.cx;
+    double ccx = ((double)i + 0.5) / N - a.center[0];
     double rr = ccx * ccx;
-    if (ND >= 2) { const double ccy = ((double)j + 0.5) / N - a.cy; rr = rr + ccy * ccy; }
-    if (ND == 3) { const double ccz = ((double)k + 0.5) / N - a.cz; rr = rr + ccz * ccz; }
+    if (ND >= 2) { const double ccy = ((double)j + 0.5) / N - a.center[1]; rr = rr + ccy * ccy; }
+    if (ND == 3) { const double ccz = ((double)k + 0.5) / N - a.center[2]; rr = rr + ccz * ccz; }
     const double rad = sqrt(rr);
     double s = (rad - a.radius - a.delta) / a.width;
     s = s < 0.0 ? 0.0 : (s > 1.0 ? 1.0 : s);
@@ -1368,6 +1364,27 @@ __global__ void __launch_bounds__(256) init_kernel(InitArgs a)
     for (int mm = 0; mm < ND; ++mm) u[(2 + mm) * ncell + idx] = (T)0;
     u[(2 + ND) * ncell + idx] = (T)(G * p);   // Et at rest
     u[(NV - 1) * ncell + idx] = (T)a2;
+}
+
+// One cloud by value, or those of a batch in one launch, its workgroups dealt
+// to the clouds in order.  A launch each took 9.5 us in turn at 32^2, 49 us at
+// 48^3 and 96^3: 24 of the former 223 us, now 14; 12 of the latter 580, now
+// 103.
+template <typename T, int ND> __global__ void __launch_bounds__(256) init_kernel(InitLaunch a)
+{
+    init_block<T, ND>(a, blockIdx.x);
+}
+template <typename T, int ND>
+__global__ void __launch_bounds__(256) init_batch_kernel(const InitLaunch* list, int count)
+{
+    const int b = blockIdx.x;
+    int lo = 0, hi = count - 1;                     // the last cloud that starts at or before b
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) / 2;
+        if (list[mid].first <= b) lo = mid; else hi = mid - 1;
+    }
+    const InitLaunch a = list[lo];
+    init_block<T, ND>(a, b - a.first);
 }
 
 // Primitive -> conserved (test states), element-wise.
@@ -1527,30 +1544,34 @@ hipError_t launch_finalize(const SampleDesc* desc, SampleState* state, const Til
     return hipGetLastError();
 }
 
+template <typename F> static void with_type(int precision, int ndim, F f)
+{
+    auto nd = [&](auto t) {
+        if (ndim == 3) f(t, std::integral_constant<int, 3>{});
+        else if (ndim == 2) f(t, std::integral_constant<int, 2>{});
+        else f(t, std::integral_constant<int, 1>{});
+    };
+    if (precision == OFM_F64) nd(double{}); else nd(float{});
+}
+
 hipError_t launch_init(int precision, int ndim, const InitLaunch& L, hipStream_t s)
 {
-    InitArgs a;
-    a.ph = L.ph;
-    a.bubbles = L.bubbles;
-    a.nb = L.nb;
-    a.n = L.n;
-    a.n_sub = L.n_sub;
-    a.rho1 = L.rho1; a.rho2 = L.rho2; a.p_bubble = L.p_bubble; a.p_inf = L.p_inf;
-    a.cx = L.center[0]; a.cy = L.center[1]; a.cz = L.center[2];
-    a.radius = L.radius; a.delta = L.delta; a.width = L.width;
-    a.u = L.u;
-    const int n = L.n;
-    int blocks;
-    if (ndim == 3) blocks = ((n + 7) / 8) * ((n + 7) / 8) * ((n + 3) / 4);
-    else if (ndim == 2) blocks = ((n + 15) / 16) * ((n + 15) / 16);
-    else blocks = (n + 255) / 256;
-#define IL(T, ND) hipLaunchKernelGGL((init_kernel<T, ND>), dim3(blocks), dim3(256), 0, s, a)
-    if (precision == OFM_F64) {
-        if (ndim == 3) IL(double, 3); else if (ndim == 2) IL(double, 2); else IL(double, 1);
-    } else {
-        if (ndim == 3) IL(float, 3); else if (ndim == 2) IL(float, 2); else IL(float, 1);
-    }
-#undef IL
+    with_type(precision, ndim, [&](auto t, auto nd) {
+        hipLaunchKernelGGL((init_kernel<decltype(t), nd()>), dim3(init_blocks<nd()>(L.n)), dim3(256), 0, s, L);
+    });
+    return hipGetLastError();
+}
+
+int init_workgroups(int ndim, int n)
+{
+    return ndim == 3 ? init_blocks<3>(n) : ndim == 2 ? init_blocks<2>(n) : init_blocks<1>(n);
+}
+
+hipError_t launch_init_batch(int precision, int ndim, const InitLaunch* list, int count, int workgroups, hipStream_t s)
+{
+    with_type(precision, ndim, [&](auto t, auto nd) {
+        hipLaunchKernelGGL((init_batch_kernel<decltype(t), nd()>), dim3(workgroups), dim3(256), 0, s, list, count);
+    });
     return hipGetLastError();
 }
 

@@ -197,6 +197,25 @@ def test_batch_in_3d_equals_single_solves(precision):
     ctx.close()
 
 
+@pytest.mark.parametrize("ndim,sizes", [(3, [9, 33, 8, 17]), (2, [16, 50, 17]), (1, [256, 700, 257])])
+def test_initial_states_of_a_batch(ctx, ndim, sizes):
+    """A batch's clouds come from one launch (none, one or many workgroups
+    each, members without bubbles among them): the same QoI after a step as
+    from a launch per cloud, bit for bit."""
+    from paper_1705_04374_amd import capi
+    say("initial states of a batch", ndim)
+    name = {1: "cloud2d", 2: "cloud2d", 3: "cloud50"}[ndim]
+    specs, bubs = [], []
+    for i, n in enumerate(sizes + sizes[:1]):
+        cfg = solver_config(name, n)
+        cfg["ndim"] = ndim
+        specs.append(capi.make_spec(cfg, "f64", n_steps=1))
+        bubs.append(np.zeros((0, 4)) if i == 1 else sample_cloud(cloud_spec(name), MASTER_SEED, 5, i))
+    qb = capi.ofm_solve_batch(ctx, specs, bubs)
+    for s, b, q in zip(specs, bubs, qb):
+        assert capi.ofm_solve(ctx, s, b) == q
+
+
 def test_autotune_times_every_candidate_and_keeps_the_fastest(ctx):
     import torch
     from paper_1705_04374_amd import capi
