@@ -48,6 +48,15 @@ template <> struct Num<float> {
     static __device__ __forceinline__ float sqrt_(float x) { return __builtin_amdgcn_sqrtf(x); }
     // sqrt(a / b) for a, b > 0 with one transcendental: a / sqrt(a b)
     static __device__ __forceinline__ float sqrt_ratio(float a, float b) { return a * __builtin_amdgcn_rsqf(a * b); }
+    // the least and the largest of three; NaN if one of them is
+    static __device__ __forceinline__ float least(float a, float b, float c)
+    {
+        return __builtin_elementwise_minimum(__builtin_elementwise_minimum(a, b), c);   // v_minimum3_f32
+    }
+    static __device__ __forceinline__ float most(float a, float b, float c)
+    {
+        return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c);
+    }
     // round-off allowance of the positivity checks, relative to the stencil
     static constexpr float round_tol = 1e-6f;
 };
@@ -72,6 +81,16 @@ template <> struct Num<double> {
         y = y * __builtin_fma(-h, y * y, 1.5);
         y = y * __builtin_fma(-h, y * y, 1.5);
         return a * y;
+    }
+    // the least and the largest of three; NaN if c is NaN (as it is where a or
+    // b is, being computed from them) or infinite
+    static __device__ __forceinline__ double least(double a, double b, double c)
+    {
+        return __builtin_fma(c, 0.0, ::fmin(::fmin(a, b), c));
+    }
+    static __device__ __forceinline__ double most(double a, double b, double c)
+    {
+        return ::fmax(::fmax(a, b), c);     // beside least, which is NaN then
     }
     static constexpr double round_tol = 1e-12;
 };
@@ -260,8 +279,9 @@ __device__ __forceinline__ void weno3_cell(T b, T c, T d, T eps, T& lo, T& hi)
 // a2 keeps its reconstruction only if it stays in [0, 1] at the same three
 // points (up to round_tol).  A variable that fails takes the cell value at
 // both edges (first order for that variable alone, so that a decision taken
-// on round-off moves the edges by round-off).  If then either edge state has
-// (Gamma+1) p + Pi <= 0, the whole cell is first order.
+// on round-off moves the edges by round-off); so does one with an edge that is
+// not a number (next to a value whose double overflows).  If then either edge
+// state has (Gamma+1) p + Pi <= 0, the whole cell is first order.
 //
 // The gas's partial density and volume fraction are exactly zero in pure
 // water, i.e. in most of a cloud's domain for the whole run.  WENO of a
@@ -293,20 +313,21 @@ __device__ __forceinline__ void edge_var(const Phys<T>& ph, int v, const T (&s)[
         weno3_cell<T>(s[1], c, s[3], ph.eps3, lo, hi);
     if (v < 2 || v == NV - 1) {
         const T mid = ORD == 5 ? (T(12) * c - lo - hi) * T(0.1) : (T(6) * c - lo - hi) * T(0.25);
-        const T least = fmin(fmin(lo, hi), mid);
+        const T least = Num<T>::least(lo, hi, mid);
         if (v < 2) {
             // the tolerance is looked up only where some lane is below zero
             if (!__all(least >= T(0))) {
                 T big = v == 0 ? ph.rho1 : ph.rho2;
 #pragma unroll
                 for (int k = K0; k < K1; ++k) big = fmax(big, fabs(s[k]));
-                const bool keep = least >= -Num<T>::round_tol * big;
+                const T tol = -Num<T>::round_tol * big;
+                // (in double an infinite interior value makes least NaN)
+                const bool keep = sizeof(T) == 4 ? least >= tol : lo >= tol && hi >= tol && mid >= tol;
                 lo = keep ? lo : c;
                 hi = keep ? hi : c;
             }
         } else {
-            const T most = fmax(fmax(lo, hi), mid);
-            const bool keep = least >= -Num<T>::round_tol && most <= T(1) + Num<T>::round_tol;
+            const bool keep = least >= -Num<T>::round_tol && Num<T>::most(lo, hi, mid) <= T(1) + Num<T>::round_tol;
             lo = keep ? lo : c;
             hi = keep ? hi : c;
         }

@@ -113,6 +113,26 @@ def test_fp64_smoothness_range(ctx, ndim, n, order, p_left, eps):
     assert np.all(err <= 1e-10), err
 
 
+@pytest.mark.parametrize("ndim,n", [(1, 64), (2, 20), (3, 16)])
+@pytest.mark.parametrize("order", [5, 3])
+def test_an_edge_that_is_not_a_number_takes_the_cell_value(ctx, ndim, n, order):
+    """Fluid at rest under one pressure, one plane of cells so dense (2e38) that
+    twice its density overflows in float: where it ends a stencil, one of the
+    two edges is NaN and the other is not.  Every flux is then the pressure
+    alone and the state stays as it is, exactly (the sound speed is 1/8)."""
+    say("nan edge", ndim, order)
+    cfg = dict(BASE, ndim=ndim, n=n, cloud_radius=0.3, ramp_delta=0.015, ramp_width=0.1, weno_order=order,
+               eos=dict(gamma1=2.0, pc1=0.25, gamma2=1.4, pc2=0.0))
+    rest = dict(a1r1=64.0, a2r2=0.0, p=0.25, a2=0.0)
+    W = riemann_primitives(ndim, n, rest, rest)
+    W[0, :, :, n // 2] = 2e38
+    U0 = oracle_shape(cfg, gpu_run(ctx, cfg, "f32", W=W)[0])
+    assert np.all(np.isfinite(U0)) and U0[0].max() > 1.9e38
+    U, q, _ = gpu_run(ctx, cfg, "f32", W=W, n_steps=4)
+    assert q["status"] == 0
+    np.testing.assert_array_equal(oracle_shape(cfg, U), U0)
+
+
 def test_fp64_ragged_tiles_and_chunks(ctx):
     """n = 20 leaves ragged tiles in x, y and z for every tile shape."""
     say("fp64 ragged 20^3")
