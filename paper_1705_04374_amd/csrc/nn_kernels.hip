@@ -580,7 +580,7 @@ phi_back_kernel(const float* __restrict__ x, const int32_t* __restrict__ offsets
                             __builtin_bit_cast(bf16x8, af), frag(&sT[(kb * 32 + lc) * RP + i * 32 + t * 16 + half * 8]),
                             dW2[kb], 0, 0, 0);
                 }
-            db2 += dsc * (float)count;
+            db2 += count ? dsc * (float)count : 0.f;    // dsc may be infinite or NaN (a label that is)
             __syncthreads();
 #pragma unroll
             for (int i = 0; i < 2; ++i) {

@@ -264,3 +264,30 @@ def test_forward_of_unaligned_rows(ctx):
     net.forward(dev(x), dev(off), y)
     net.forward(xs, dev(off), ys)
     assert torch.equal(y, ys)
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_gradients_beside_a_label_that_is_not_finite(ctx, bad):
+    """A label that is not finite spoils the gradients of the units that are
+    active on its set's one bubble, and no others: theirs are those of the
+    other sets (the bars of the small batch)."""
+    import torch
+    say("nn grads, label", bad)
+    p, x, off, t = problem(9, [70, 1, 130])
+    y, c = N.forward(p, x, off, 1.0 / 500, bf16_ops=True)
+    net = gpu_net(ctx, p, 1.0 / 500)
+    g = torch.zeros(N.param_count(), dtype=torch.float32, device="cuda")
+    loss = torch.zeros(1, dtype=torch.float32, device="cuda")
+    tb = t.copy()
+    tb[1, 2] = bad
+    net.grads(dev(x), dev(off), dev(tb), g, loss)
+    gg = N.unflatten(g.cpu().numpy().astype(np.float64))
+    t[1] = y[1]                          # that set's part of the gradients is zero
+    _, ref = N.loss_and_grads(p, x, off, 1.0 / 500, t, bf16_ops=True)
+    off_units = c["z2"][70] < -1e-3      # not active on the bubble, by more than the kernels' rounding
+    on_units = c["z2"][70] > 1e-3
+    assert 20 < off_units.sum() and 20 < on_units.sum()
+    assert not np.isfinite(gg["b2"][on_units]).any()
+    for k in ("b2", "W2"):
+        assert np.isfinite(gg[k][off_units]).all(), k
+        assert rel(gg[k][off_units], ref[k][off_units]) <= 1e-3, k
