@@ -236,12 +236,12 @@ int ofm_step(ofm_ctx* ctx, const ofm_solve_spec* spec, ofm_state_view* st, int64
  * launches, on the caller's stream, with
  * the same results bit for bit; it calls no hipMalloc, hipHostMalloc or
  * hipFree and creates no events.  Its scratch (the sample's descriptor and
- * dynamic state, 64 B of reduction partial and 8 B of work list per tile of
- * the tuned tiling, and 8 B per step when dts is given) is a fixed device
- * array of OFM_NOALLOC_SCRATCH_BYTES per GPU, kept until the process ends;
- * a call that needs more (e.g. a 16 x 16 x 16 tiling of a 1024^3 grid, or a
- * step log longer than about 500 000 steps) returns OFM_EINVAL before any
- * launch.  Every call on one GPU shares that array: calls that overlap in
+ * dynamic state, 72 B of reduction partial per tile, and 8 B per step when
+ * dts is given) is a fixed device array of OFM_NOALLOC_SCRATCH_BYTES per GPU,
+ * kept until the process ends.  Where no tiling was set for the size
+ * (ofm_tune_set, ofm_autotune) the fastest that fits beside the step log is
+ * taken; a call that needs more (e.g. a 1024^3 grid, or a step log longer
+ * than about 500 000 steps) returns OFM_EINVAL before any launch.  Every call on one GPU shares that array: calls that overlap in
  * time on one GPU (other streams, other threads) race and must be
  * serialised by the caller.  Arguments, results and u/u_tmp exchange as for
  * ofm_step; per-launch kernel timing (ofm_kernel_timing) does not apply.

@@ -308,7 +308,7 @@ static int run_begin(ofm_ctx* ctx, ofm_run& r, bool init, int64_t dts_len, hipSt
     // tiling
     std::vector<int> sizes;
     for (const Member& m : mem) sizes.push_back(m.spec.n);
-    r.tc = ctx->tuning.choose(prec, nd, sizes);
+    r.tc = ctx->tuning.choose(prec, nd, sizes.data(), ns);
     const TileChoice& tc = r.tc;
     r.desc.assign(ns, SampleDesc{});
     int tiles = 0;
@@ -586,8 +586,8 @@ static void to_qoi(const ofm_solve_spec& s, const SampleState& st, ofm_qoi* q)
 // Stepping without allocation (ofm_step_noalloc)
 // ---------------------------------------------------------------------------
 // The stepper's scratch lives in a fixed device array: the sample
-// descriptor, its dynamic state, one reduction partial per tile, the work
-// list and the step-size log.  Every GPU the library runs on holds its own
+// descriptor, its dynamic state, one reduction partial per tile and the
+// step-size log.  Every GPU the library runs on holds its own
 // copy until the process ends; all calls on that GPU share it.
 static __device__ __align__(256) unsigned char scratch[OFM_NOALLOC_SCRATCH_BYTES];
 
@@ -770,24 +770,22 @@ int ofm_step_noalloc(ofm_ctx* ctx, const ofm_solve_spec* spec, ofm_state_view* s
     ofm_solve_spec s = *spec;
     s.n_steps = n_steps;
     s.max_steps = n_steps;
-    // scratch layout: descriptor | state | partials | step sizes
+    // scratch layout: descriptor | state | partials | step sizes; the tiling
+    // keeps to the tiles that the step sizes leave room for
     const size_t o_state = align256(sizeof(SampleDesc));
     const size_t o_part = align256(o_state + sizeof(SampleState));
-    auto log_at = [&](const SampleDesc& d) { return align256(o_part + sizeof(TilePartial) * (size_t)d.ntiles); };
     const size_t log_bytes = dts ? sizeof(double) * (size_t)n_steps : 0;
-    // a long log leaves room for few tiles: the tiling with fewer then
-    TileChoice tc = ctx->tuning.choose(s.precision, s.ndim, { s.n });
-    SampleDesc d = make_desc(s, tc, 0, st->u, st->u_tmp, st->du);
-    if (log_at(d) + log_bytes > (size_t)OFM_NOALLOC_SCRATCH_BYTES && !ctx->tuning.has(s.precision, s.ndim, s.n)) {
-        tc = Tuning::general(s.precision, s.ndim, s.n);
-        d = make_desc(s, tc, 0, st->u, st->u_tmp, st->du);
-    }
-    const size_t o_dt = log_at(d);
+    const size_t scratch_bytes = OFM_NOALLOC_SCRATCH_BYTES;
+    const size_t room = log_bytes < scratch_bytes ? (scratch_bytes - log_bytes) / 256 * 256 : 0;
+    const int64_t most_tiles = room > o_part ? (int64_t)((room - o_part) / sizeof(TilePartial)) : 0;
+    const TileChoice tc = ctx->tuning.choose(s.precision, s.ndim, &s.n, 1, most_tiles);
+    const SampleDesc d = make_desc(s, tc, 0, st->u, st->u_tmp, st->du);
+    const size_t o_dt = align256(o_part + sizeof(TilePartial) * (size_t)d.ntiles);
     const size_t need = o_dt + log_bytes;
-    if (need > (size_t)OFM_NOALLOC_SCRATCH_BYTES)
+    if (need > scratch_bytes)
         return fail(ctx, OFM_EINVAL,
                     "ofm_step_noalloc: %d tiles%s need %zu bytes of scratch; the fixed scratch holds %zu",
-                    d.ntiles, dts ? " and the step-size log" : "", need, (size_t)OFM_NOALLOC_SCRATCH_BYTES);
+                    d.ntiles, dts ? " and the step-size log" : "", need, scratch_bytes);
     HIPCHK(ctx, hipSetDevice(ctx->device));
     char* base = scratch_of(ctx);
     if (!base) return fail(ctx, OFM_EHIP, "ofm_step_noalloc: scratch of device %d not resolved", ctx->device);
@@ -974,7 +972,7 @@ int ofm_tune_get(const ofm_ctx* ctx, int32_t precision, int32_t ndim, int32_t n,
     if (!ctx || !out) return fail(nullptr, OFM_EINVAL, "ofm_tune_get: null argument");
     if (ndim < 1 || ndim > 3 || (precision != OFM_F32 && precision != OFM_F64) || n < 1)
         return fail(const_cast<ofm_ctx*>(ctx), OFM_EINVAL, "ofm_tune_get: bad precision, ndim or n");
-    const TileChoice t = ctx->tuning.choose(precision, ndim, { n });
+    const TileChoice t = ctx->tuning.choose(precision, ndim, &n, 1);
     *out = ofm_tune_result{ t.tx, t.ty, t.zchunk, t.graph_steps, 0.0, 0, 0 };
     return OFM_OK;
 }
@@ -1013,7 +1011,7 @@ int ofm_autotune(ofm_ctx* ctx, const ofm_solve_spec* spec, ofm_state_view* st, i
         if (z.empty()) z.push_back(spec->n);
         return z;
     };
-    const TileChoice before = ctx->tuning.choose(spec->precision, spec->ndim, { spec->n });
+    const TileChoice before = ctx->tuning.choose(spec->precision, spec->ndim, &spec->n, 1);
     const bool had_timing = ctx->timing;
     const int64_t l0 = ctx->t_launches;
     const double m0 = ctx->t_ms, c0 = ctx->t_cells;

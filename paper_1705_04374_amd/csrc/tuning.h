@@ -8,7 +8,6 @@
 #include <cstdint>
 #include <map>
 #include <tuple>
-#include <vector>
 
 namespace ofm {
 
@@ -28,8 +27,25 @@ struct Tuning {
         return c;
     }
 
-    // The tiling where nothing was set: the one with the least estimated time
-    // of a stage launch over all the samples of a run.
+    // The entry that applies to a run whose largest grid has n cells per side,
+    // or null.
+    const TileChoice* entry(int precision, int ndim, int n) const
+    {
+        auto it = table.find(std::make_tuple(precision, ndim, size_class(n)));
+        return it != table.end() ? &it->second : nullptr;
+    }
+
+    // The tiling of a run of count samples: the entry that was set, else the
+    // default.  most_tiles: the tiles that the caller has room for (the default
+    // keeps to it where a tiling of no more tiles than general()'s does).
+    TileChoice choose(int precision, int ndim, const int* sizes, int count, int64_t most_tiles = INT64_MAX) const
+    {
+        const TileChoice* set = entry(precision, ndim, *std::max_element(sizes, sizes + count));
+        return set ? *set : fastest(precision, ndim, sizes, count, most_tiles);
+    }
+
+    // The default: the tiling with the least estimated time of a stage launch
+    // over all the samples of a run.
     //
     // A workgroup takes `z` planes of its tile one after the other, plus `ends`
     // planes' work at the chunk's two ends (its latency counts less where a CU
@@ -45,17 +61,23 @@ struct Tuning {
     // -> 6235, 200^3 the same.
     // Tilings give the same results bit for bit, so that a batch's choice can
     // follow its total without changing any sample's.
-    TileChoice choose(int precision, int ndim, const std::vector<int>& sizes) const
+    static TileChoice fastest(int precision, int ndim, const int* sizes, int count, int64_t most_tiles)
     {
-        const int maxn = *std::max_element(sizes.begin(), sizes.end());
-        auto it = table.find(std::make_tuple(precision, ndim, size_class(maxn)));
-        if (it != table.end()) return it->second;
+        const int maxn = *std::max_element(sizes, sizes + count);
         TileChoice t = general(precision, ndim, maxn);
+        if (maxn > kMostCells) return t;            // no solve takes it
         const bool dbl = precision == 1;
+        const auto tiles = [&](int tx, int ty, int z) {
+            int64_t k = 0;
+            for (int i = 0; i < count; ++i)
+                k += (int64_t)((sizes[i] + tx - 1) / tx) * (ndim < 2 ? 1 : (sizes[i] + ty - 1) / ty) *
+                     (ndim < 3 ? 1 : (sizes[i] + z - 1) / z);
+            return k;
+        };
         if (ndim == 1) {
             // 4 steps with 64 cells a tile against 256 (us): 64 cells 188
             // against 197, 256 194 and 204, 4000 189 and 196
-            t.tx = 64;
+            if (tiles(64, 1, 1) <= most_tiles) t.tx = 64;
             return t;
         }
         if (ndim == 2) {
@@ -64,21 +86,16 @@ struct Tuning {
             // (4 steps, us: 64^2 218 against 233, 256^2 255 and 285, 320^2
             // 345 and 291).  float: 16 x 16 where that saves a second tile a
             // CU (256^2 218 against 236; 160^2 216 and 211, 320^2 252 and 237).
-            const auto tiles2 = [&](int ty) {
-                int64_t k = 0;
-                for (int n : sizes) k += (int64_t)((n + 15) / 16) * ((n + ty - 1) / ty);
-                return k;
-            };
-            if (dbl) t.ty = tiles2(8) <= 2 * kCUs ? 8 : 14;
-            else t.ty = tiles2(16) <= kCUs && tiles2(14) > kCUs ? 16 : 14;
+            if (dbl) t.ty = tiles(16, 8, 1) <= std::min<int64_t>(2 * kCUs, most_tiles) ? 8 : 14;
+            else t.ty = tiles(16, 16, 1) <= kCUs && tiles(16, 14, 1) > kCUs ? 16 : 14;
             return t;
         }
         const double slope = dbl ? 0.81 : 0.48, base = dbl ? 0.0 : 0.35, least = dbl ? 1.1 : 1.0;
         double best = INFINITY;
         for (int ty : { 14, 16 })
             for (int z : { 32, 24, 16, 12, 8, 6, 4, 3, 2, 1 }) {
-                const int64_t n_tiles = tiles(sizes, 16, ty, z);
-                if (n_tiles > kMaxTiles) continue;
+                const int64_t n_tiles = tiles(16, ty, z);
+                if (n_tiles > std::min(kMaxTiles, most_tiles)) continue;
                 // a plane of a 16 x 16 tile against one of 16 x 14: more cells,
                 // but (in double above all) less of the GPU's latency hidden
                 const double plane = ty == 14 ? 1.0 : dbl ? 1.35 : 1.17;
@@ -94,8 +111,8 @@ struct Tuning {
         return t;
     }
 
-    // Fewer tiles, for grids beyond kMaxTiles and where the tiles' scratch is
-    // limited.
+    // The tiling by the largest grid alone: of runs where every other would
+    // have more than kMaxTiles, or more than there is room for.
     static TileChoice general(int precision, int ndim, int maxn)
     {
         TileChoice t;
@@ -116,20 +133,10 @@ struct Tuning {
         return t;
     }
 
-    static int64_t tiles(const std::vector<int>& sizes, int tx, int ty, int z)
-    {
-        int64_t k = 0;
-        for (int n : sizes) k += (int64_t)((n + tx - 1) / tx) * ((n + ty - 1) / ty) * ((n + z - 1) / z);
-        return k;
-    }
-
     static constexpr int kCUs = 256;            // of the GPU
-    static constexpr int64_t kMaxTiles = 32768; // of a default tiling: 2.3 MB of partials
-
-    bool has(int precision, int ndim, int n) const
-    {
-        return table.count(std::make_tuple(precision, ndim, size_class(n))) != 0;
-    }
+    static constexpr int kMostCells = 4096;     // per side of a grid
+    // of the tilings among which the default is chosen (2.3 MB of partials)
+    static constexpr int64_t kMaxTiles = 32768;
 
     void set(int precision, int ndim, int n, const TileChoice& t)
     {
