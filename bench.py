@@ -338,9 +338,10 @@ def main():
         kt64 = r64["kt"]
         ms64 = kt64["total_ms"] / max(kt64["launches"], 1)
         c64 = kt64["cells"] / max(kt64["launches"], 1)
+        used64 = capi.ofm_tune_get(ctx, capi.OFM_F64, 3, n)
         out["fp64"] = {"value": cells * max(4, a.steps // 3) / r64["wall"], "unit": "cell-updates/s",
                        "avg_stage_launch_ms": round(ms64, 4),
-                       "tile": None if r64["tuned"] is None else {k: r64["tuned"][k] for k in ("tx", "ty", "zchunk")},
+                       "tile": None if r64["tuned"] is None else {k: used64[k] for k in ("tx", "ty", "zchunk")},
                        "hbm_frac": round(c64 * WORDS_PER_CELL_STEP * 8 / 3.0 / (ms64 * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                        "alu_frac": round(c64 * FLOPS_PER_CELL_STAGE / (ms64 * 1e-3) / 1e12 / VALU_PEAK_TFLOPS["f64"], 4)}
     if not a.no_weno3 and a.precision == "f32":

@@ -321,13 +321,17 @@ int ofm_tune_get(const ofm_ctx* ctx, int32_t precision, int32_t ndim, int32_t n,
  * 64 planes not larger than n, and those whose workgroup count fills 1 to 8
  * whole rounds of the device's CUs at the tile's occupancy) of the stage kernel for spec's precision,
  * dimension and grid, by stepping the caller's state st [dev] `steps` time
- * steps per candidate with per-launch events, and store the fastest as the
- * entry ofm_tune_set would write; out [host] receives it.  The state is
- * advanced (candidates x steps steps, u and u_tmp may swap as in ofm_step):
- * pass a scratch copy.  all [host, may be NULL] receives up to all_cap
- * entries, one per candidate in the order timed (candidates = 1 each).  On
- * an error the previous entry is kept; OFM_EINVAL also if the state fails
- * (non-finite, c^2 <= 0) while stepping.  Synchronises the stream. */
+ * steps per candidate with per-launch events; out [host] receives the fastest
+ * candidate.  It is stored as the entry ofm_tune_set would write, unless what
+ * solves of this size use without it (the entry there is, or the default,
+ * timed after the candidates) is faster: then that stays (ofm_tune_get tells;
+ * the default follows each run's own sizes, an entry serves its whole size
+ * class).  The state is advanced (up to (candidates + 1) x steps steps, u and
+ * u_tmp may swap as in ofm_step): pass a scratch copy.  all [host, may be
+ * NULL] receives up to all_cap entries, one per candidate in the order timed
+ * (candidates = 1 each).  On an error the entry, or that there was none, is
+ * kept; OFM_EINVAL also if the state fails (non-finite, c^2 <= 0) while
+ * stepping.  Synchronises the stream. */
 int ofm_autotune(ofm_ctx* ctx, const ofm_solve_spec* spec, ofm_state_view* st, int32_t steps,
                  ofm_tune_result* out, ofm_tune_result* all, int32_t all_cap, void* stream);
 

@@ -1,6 +1,7 @@
 // Tile / schedule choice of the stage kernel per (precision, dimension, size).
 // Defaults are set here; ofm_tune_set overrides one entry and ofm_autotune
-// measures the compiled candidates and stores the fastest.
+// measures the compiled candidates and stores the fastest unless what is used
+// without it is faster.
 #pragma once
 
 #include <algorithm>
@@ -142,6 +143,8 @@ struct Tuning {
     {
         table[std::make_tuple(precision, ndim, size_class(n))] = t;
     }
+
+    void erase(int precision, int ndim, int n) { table.erase(std::make_tuple(precision, ndim, size_class(n))); }
 };
 
 }  // namespace ofm

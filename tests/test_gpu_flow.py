@@ -261,6 +261,59 @@ def test_autotune_times_every_candidate_and_keeps_the_fastest(ctx):
     torch.cuda.empty_cache()
 
 
+TILE = ("tx", "ty", "zchunk", "graph_steps")
+
+
+def tiling(ctx, capi, n):
+    r = capi.ofm_tune_get(ctx, capi.OFM_F32, 3, n)
+    return tuple(r[k] for k in TILE)
+
+
+@pytest.mark.parametrize("failing", [False, True])
+def test_autotune_leaves_a_default_that_is_faster(failing):
+    """At 48^3 the default's chunks of one plane take a third of the time of
+    any candidate; and a state that fails while stepping is an error.  Either
+    way no entry is stored, so that other sizes of the class (64^3) and
+    batches keep their own default; an entry that was set stays."""
+    import torch
+    from paper_1705_04374_amd import capi
+    say("autotune, default kept", failing)
+    ctx = capi.Context(0)
+    cfg = solver_config("cloud50", 48)
+    spec = capi.make_spec(cfg, "f32", n_steps=2)
+    st, bufs = alloc_state(cfg, "f32")
+    capi.ofm_state_init(ctx, spec, sample_cloud(cloud_spec("cloud50"), MASTER_SEED, 0, 6), st)
+    if failing:
+        torch.cuda.synchronize()
+        bufs[0].view(-1)[5] = float("nan")
+    before = [tiling(ctx, capi, n) for n in (48, 64, 40)]
+    for entry in (None, (16, 14, 1, 8)):
+        if entry:
+            capi.ofm_tune_set(ctx, capi.OFM_F32, 3, 48, *entry)
+        if failing:
+            with pytest.raises(capi.OfmError):
+                capi.ofm_autotune(ctx, spec, st, 2)
+        else:
+            r = capi.ofm_autotune(ctx, spec, st, 2)
+            assert (r["tx"], r["ty"], r["zchunk"]) == min(r["table"], key=lambda t: t[3])[:3]
+        assert [tiling(ctx, capi, n) for n in (48, 64, 40)] == ([entry] * 3 if entry else before)
+    ctx.close()
+
+
+def test_autotune_replaces_a_slower_entry(ctx):
+    from paper_1705_04374_amd import capi
+    say("autotune, entry replaced")
+    cfg = solver_config("cloud50", 128)
+    spec = capi.make_spec(cfg, "f32", n_steps=2)
+    st, bufs = alloc_state(cfg, "f32")
+    own = capi.Context(0)
+    capi.ofm_state_init(own, spec, sample_cloud(cloud_spec("cloud50"), MASTER_SEED, 0, 6), st)
+    capi.ofm_tune_set(own, capi.OFM_F32, 3, 128, 16, 8, 1, 4)     # 16384 tiles of one plane
+    r = capi.ofm_autotune(own, spec, st, 2)
+    assert tiling(own, capi, 128) == (r["tx"], r["ty"], r["zchunk"], 4)
+    own.close()
+
+
 @pytest.mark.parametrize("case", ["sod", "water_air"])
 def test_fp64_shock_tube(ctx, case):
     say("shock tube", case)
