@@ -193,6 +193,8 @@ struct ofm_run {
     double* d_dt = nullptr;
     ofm::WorkItem* d_work = nullptr;
     int most_tiles = 0;         // of a member
+    int room = 0;               // tiles that the partials and the work list have room for
+    bool tuned = false;         // the tiling was set, not chosen
     std::vector<int> order;                 // samples, larger grids first
     int64_t dts_len = 0;
     hipGraph_t graph = nullptr;
@@ -255,28 +257,65 @@ static int run_capture(ofm_run& r)
     return OFM_OK;
 }
 
-// Drop the tiles of finished samples from the work list once they are more
-// than a tenth of it.  The launch index is mapped to work items in
-// contiguous ranges per XCD, so tiles that exit at once would otherwise
-// leave some XCDs idle while others carry the live samples; the graph is
-// captured again for the shorter grid.  Results do not depend on the tile
-// order (each cell's arithmetic and each sample's reduction order are fixed).
+// Descriptors of the samples that are not done (all before the first step)
+// under the run's tiling, and its work list: larger samples first, tiles of a
+// sample contiguous (a run of one sample needs none).
+static void run_tiles(ofm_run& r, std::vector<WorkItem>& work)
+{
+    int tiles = 0;
+    r.most_tiles = 0;
+    work.clear();
+    for (size_t i = 0; i < r.mem.size(); ++i) {
+        if (r.state[i].done) continue;
+        const Member& m = r.mem[i];
+        r.desc[i] = make_desc(m.spec, r.tc, tiles, m.buf0, m.buf1, m.du);
+        tiles += r.desc[i].ntiles;
+        r.most_tiles = std::max(r.most_tiles, r.desc[i].ntiles);
+    }
+    if (r.mem.size() > 1) {
+        work.reserve(tiles);
+        for (int i : r.order)
+            if (!r.state[i].done)
+                for (int t = 0; t < r.desc[i].ntiles; ++t) work.push_back(WorkItem{ i, t });
+    }
+    r.la.n_work = tiles;
+    r.la.zchunk = r.tc.zchunk;
+}
+
+// Once the tiles of finished samples are more than a tenth of the work list:
+// tile the others anew and list their tiles.  The launch index is mapped to
+// work items in contiguous ranges per XCD, so tiles that exit at once would
+// otherwise leave some XCDs idle while others carry the live samples; and few
+// samples take shorter chunks than many (stage launches of 40 steps of the
+// last 64^3 sample of 61: 9.3 ms in float and 36.9 in double with the tiling
+// of them all, 4.0 and 6.7 with its own).  A tiling that was set stays, as do
+// K and the room for the tiles.  The graph is captured again.  Results depend neither on the tile order nor on the
+// tiling (each cell's arithmetic is fixed; Sum2).
 static int run_compact(ofm_run& r)
 {
     int64_t live = 0;
+    std::vector<int> sizes;
     for (size_t i = 0; i < r.mem.size(); ++i)
-        if (!r.host_state[i].done) live += r.desc[i].ntiles;
+        if (!r.state[i].done) {
+            live += r.desc[i].ntiles;
+            sizes.push_back(r.mem[i].spec.n);
+        }
     if (live == 0 || (double)live > 0.9 * (double)r.la.n_work) return OFM_OK;
-    std::vector<WorkItem> work;
-    work.reserve(live);
-    for (int i : r.order)
-        if (!r.host_state[i].done)
-            for (int t = 0; t < r.desc[i].ntiles; ++t) work.push_back(WorkItem{ i, t });
     ofm_ctx* ctx = r.ctx;
+    const ofm_solve_spec& s0 = r.mem[0].spec;
+    std::vector<WorkItem> work;
+    const TileChoice before = r.tc;
+    if (!r.tuned) r.tc = Tuning::fastest(s0.precision, s0.ndim, sizes.data(), (int)sizes.size(), r.room);
+    run_tiles(r, work);
+    if (r.la.n_work > r.room) {             // (no tiling that fits is among the choices)
+        r.tc = before;
+        run_tiles(r, work);
+    }
+    HIPCHK(ctx, hipMemcpyAsync(r.d_desc, r.desc.data(), sizeof(SampleDesc) * r.desc.size(), hipMemcpyHostToDevice,
+                               ctx->stream));
     HIPCHK(ctx, hipMemcpyAsync(r.d_work, work.data(), sizeof(WorkItem) * work.size(), hipMemcpyHostToDevice,
                                ctx->stream));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    r.la.n_work = (int)work.size();
     return r.eager ? OFM_OK : run_capture(r);
 }
 
@@ -308,26 +347,19 @@ static int run_begin(ofm_ctx* ctx, ofm_run& r, bool init, int64_t dts_len, hipSt
     // tiling
     std::vector<int> sizes;
     for (const Member& m : mem) sizes.push_back(m.spec.n);
+    r.tuned = ctx->tuning.entry(prec, nd, *std::max_element(sizes.begin(), sizes.end())) != nullptr;
     r.tc = ctx->tuning.choose(prec, nd, sizes.data(), ns);
     const TileChoice& tc = r.tc;
-    r.desc.assign(ns, SampleDesc{});
-    int tiles = 0;
-    for (int i = 0; i < ns; ++i) {
-        r.desc[i] = make_desc(mem[i].spec, tc, tiles, mem[i].buf0, mem[i].buf1, mem[i].du);
-        tiles += r.desc[i].ntiles;
-        r.most_tiles = std::max(r.most_tiles, r.desc[i].ntiles);
-    }
-    // work list: larger samples first, tiles of a sample contiguous (one
-    // sample needs none)
     r.order.resize(ns);
     for (int i = 0; i < ns; ++i) r.order[i] = i;
     std::stable_sort(r.order.begin(), r.order.end(), [&](int a, int b) { return mem[a].spec.n > mem[b].spec.n; });
+    r.desc.assign(ns, SampleDesc{});
+    r.state.resize(ns);
+    for (SampleState& s : r.state) memset(&s, 0, sizeof s);
     std::vector<WorkItem> work;
-    if (ns > 1) {
-        work.reserve(tiles);
-        for (int i : r.order)
-            for (int t = 0; t < r.desc[i].ntiles; ++t) work.push_back(WorkItem{ i, t });
-    }
+    run_tiles(r, work);
+    const int tiles = r.la.n_work;
+    r.room = tiles;
 
     const size_t o_desc = 0;
     const size_t o_state = align256(o_desc + sizeof(SampleDesc) * ns);
@@ -360,10 +392,8 @@ static int run_begin(ofm_ctx* ctx, ofm_run& r, bool init, int64_t dts_len, hipSt
     r.d_work = ns > 1 ? (WorkItem*)(meta + o_work) : nullptr;
     r.d_dt = dts_len > 0 ? (double*)(meta + o_dt) : nullptr;
 
-    std::vector<SampleState> st0(ns);
-    for (auto& s : st0) memset(&s, 0, sizeof s);
     HIPCHK(ctx, hipMemcpyAsync(r.d_desc, r.desc.data(), sizeof(SampleDesc) * ns, hipMemcpyHostToDevice, stream));
-    HIPCHK(ctx, hipMemcpyAsync(r.d_state, st0.data(), sizeof(SampleState) * ns, hipMemcpyHostToDevice, stream));
+    HIPCHK(ctx, hipMemcpyAsync(r.d_state, r.state.data(), sizeof(SampleState) * ns, hipMemcpyHostToDevice, stream));
     if (ns > 1)
         HIPCHK(ctx, hipMemcpyAsync(r.d_work, work.data(), sizeof(WorkItem) * work.size(), hipMemcpyHostToDevice, stream));
 
@@ -419,8 +449,6 @@ static int run_begin(ofm_ctx* ctx, ofm_run& r, bool init, int64_t dts_len, hipSt
     LaunchArgs& la = r.la;
     la.ph = ph;
     la.work = r.d_work;
-    la.n_work = tiles;
-    la.zchunk = tc.zchunk;
     la.desc = r.d_desc;
     la.state = r.d_state;
     la.part = r.d_part;
@@ -446,7 +474,6 @@ static int run_begin(ofm_ctx* ctx, ofm_run& r, bool init, int64_t dts_len, hipSt
     }
     r.live_cells = 0.0;
     for (int i = 0; i < ns; ++i) r.live_cells += (double)cells_of(mem[i].spec);
-    r.state.assign(st0.begin(), st0.end());
     if (!r.eager) return run_capture(r);
     return OFM_OK;
 }

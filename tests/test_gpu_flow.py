@@ -217,6 +217,66 @@ def test_batch_in_3d_equals_single_solves(precision):
     ctx.close()
 
 
+@pytest.mark.parametrize("name,precision,members", [
+    ("cloud50", "f64", [(64, 2)] * 12 + [(20, 21)] * 3 + [(64, 37), (48, 60), (20, 75)]),
+    ("cloud50", "f32", [(32, 2)] * 40 + [(32, 20)] * 9 + [(96, 33), (32, 52)]),
+    ("cloud2d", "f64", [(64, 2)] * 40 + [(200, 19), (64, 40), (33, 70)]),
+    ("cloud2d", "f32", [(255, 2)] + [(64, 2)] * 30 + [(256, 35), (33, 70)])])
+@pytest.mark.parametrize("tuned", [False, True])
+def test_a_batch_whose_members_finish_in_turn(name, precision, members, tuned):
+    """The tiling follows the members that are left: each sample's QoI stays
+    what it is alone, bit for bit, also with a tiling that was set, in one call
+    and advanced in portions."""
+    from paper_1705_04374_amd import capi
+    say("members finish in turn", name, precision, tuned)
+    ctx = capi.Context(0)
+    ndim = 2 if name == "cloud2d" else 3
+    if tuned:
+        most = max(n for n, _ in members)
+        capi.ofm_tune_set(ctx, capi.OFM_F64 if precision == "f64" else capi.OFM_F32, ndim, most, 16, 14, 8 if ndim == 3 else 1, 4)
+    specs = [capi.make_spec(solver_config(name, n), precision, n_steps=k) for n, k in members]
+    bubs = [sample_cloud(cloud_spec(name), MASTER_SEED, 6, i % 4) for i in range(len(members))]
+    qb = capi.ofm_solve_batch(ctx, specs, bubs)
+    alone = {}
+    for i, (m, s, b, q) in enumerate(zip(members, specs, bubs, qb)):
+        key = m + (i % 4,)
+        if key not in alone:
+            alone[key] = capi.ofm_solve(ctx, s, b)
+        assert alone[key] == q, (i, m)
+    run = capi.Run(ctx, specs, bubs)
+    while not run.advance(5):
+        pass
+    assert run.status()["qoi"] == qb
+    run.close()
+    ctx.close()
+
+
+@pytest.mark.parametrize("precision", ["f32", "f64"])
+def test_the_last_member_of_a_batch_is_tiled_as_if_alone(precision):
+    """Stage time of 40 more steps of one 64^3 sample as the last of 61 (whose
+    chunks of 32 planes would take at least twice as long), and alone."""
+    from paper_1705_04374_amd import capi
+    say("last member", precision)
+    ctx = capi.Context(0)
+    bub = sample_cloud(cloud_spec("cloud50"), MASTER_SEED, 0, 6)
+
+    def stage_ms(others, steps):
+        specs = [capi.make_spec(solver_config("cloud50", 64), precision, n_steps=k) for k in [2] * others + [steps]]
+        best = math.inf
+        for _ in range(3):
+            capi.ofm_kernel_timing(ctx, True)
+            capi.ofm_solve_batch(ctx, specs, [bub] * len(specs))
+            best = min(best, capi.ofm_kernel_times(ctx)["total_ms"])
+            capi.ofm_kernel_timing(ctx, False)
+        return best
+
+    last = stage_ms(60, 42) - stage_ms(60, 2)
+    alone = stage_ms(0, 42) - stage_ms(0, 2)
+    say("  last %.3f ms, alone %.3f ms" % (last, alone))
+    assert last <= 1.5 * alone
+    ctx.close()
+
+
 @pytest.mark.parametrize("ndim,sizes", [(3, [9, 33, 8, 17]), (2, [16, 50, 17]), (1, [256, 700, 257])])
 def test_initial_states_of_a_batch(ctx, ndim, sizes):
     """A batch's clouds come from one launch (none, one or many workgroups
