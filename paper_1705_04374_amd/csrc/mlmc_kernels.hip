@@ -34,9 +34,12 @@ template <int NT> __device__ __forceinline__ void block_sum3(double (&v)[3])
 // Moments of one term: (M_used, mean_f, mean_c, Var_f, Var_c, Cov), two-pass,
 // by one workgroup.  Bound by the latency of its loads: each thread has those
 // of eight samples in flight (of 16: half the speed, at 128 registers a
-// thread), and there are 16 wavefronts from 1024 samples on.  65536 samples
+// thread), and there are 16 wavefronts where 4 would take more than four such
+// groups in turn: from 8192 samples (the kernel alone, us, without and with
+// coarse values: 1024 samples 3.7 and 4.2 with 4, 8.3 and 9.4 with 16; 6000,
+// 6.8 and 8.0, 8.4 and 9.4; 8192, 8.1 and 10.0, 8.4 and 9.5).  65536 samples
 // without coarse values: 119 us before (4 wavefronts, a sample at a time, six
-// sums through LDS), 31 now; 3276 samples 12.7 and 9.8; 10^6, 5450 and 570.
+// sums through LDS), 31 now; 3276 samples 10.2 and 5.4; 10^6, 5450 and 570.
 template <int NT>
 __global__ void __launch_bounds__(NT) moments_kernel(const double* __restrict__ qf, const double* __restrict__ qc,
                                                      const int32_t* __restrict__ ok, int64_t M,
@@ -346,7 +349,7 @@ hipError_t launch_fit(int L, int first, int m_floor, double* mom, double* vhat, 
 hipError_t launch_moments(const double* qf, const double* qc, const int32_t* ok, int64_t M, double* out,
                           hipStream_t s)
 {
-    if (M < 1024)
+    if (M < 8192)
         hipLaunchKernelGGL((moments_kernel<256>), dim3(1), dim3(256), 0, s, qf, qc, ok, M, out);
     else
         hipLaunchKernelGGL((moments_kernel<1024>), dim3(1), dim3(1024), 0, s, qf, qc, ok, M, out);

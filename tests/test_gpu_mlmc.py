@@ -103,6 +103,26 @@ def test_moments_at_the_edges_of_their_launches(ctx, M, paired):
             assert abs(g - r[k]) <= 1e-12 * max(abs(r[k]), 1e-300), (k, g, r[k])
 
 
+@pytest.mark.parametrize("M", [2047, 2049, 6144, 8191, 8192])
+def test_moments_around_the_line_between_their_launches(ctx, M):
+    """One to four groups of loads a thread, and the first launch of sixteen
+    wavefronts, with the last sample left out (<= 1e-12 relative)."""
+    import torch
+    from paper_1705_04374_amd import capi
+    rng = np.random.default_rng(M)
+    y = rng.normal(size=M)
+    qf, qc = 3.0 + y, 5.0 + y + 0.5 * rng.normal(size=M)
+    ok = np.ones(M, np.int32)
+    ok[-1] = 0
+    r = O.term_moments(qf, qc, ok.astype(bool))
+    out = torch.full((6,), -1.0, dtype=torch.float64, device="cuda")
+    capi.ofm_mlmc_moments(ctx, *(torch.tensor(v, device="cuda") for v in (qf, qc, ok)), out)
+    got = out.cpu().tolist()
+    assert got[0] == r["M"] == M - 1
+    for g, k in zip(got[1:], ("mean_f", "mean_c", "Vf", "Vc", "C")):
+        assert abs(g - r[k]) <= 1e-12 * max(abs(r[k]), 1e-300), (k, g, r[k])
+
+
 @pytest.mark.parametrize("L", [0, 1, 5, 31])
 def test_sample_counts_with_terms_fixed_in_turn(ctx, L):
     """Terms that hold more samples than their optimum are fixed one after
