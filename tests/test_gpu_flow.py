@@ -16,7 +16,7 @@ import pytest
 import oracle.flow as OF
 from oracle.sampler import sample_cloud
 from workloads.configs import (BASE, EOS, MASTER_SEED, cloud_spec, interface_primitives,
-                               riemann_primitives, solver_config)
+                               random_smooth_primitives, riemann_primitives, solver_config)
 from helpers import alloc_state, max_rel_field, oracle_shape, read_state, rel_l1
 
 pytestmark = pytest.mark.gpu
@@ -401,6 +401,50 @@ def test_fp64_periodic_interface(ctx):
     U, _, _ = gpu_run(ctx, cfg, "f64", W=W, n_steps=40)
     R, _ = OF.run_steps(cfg, OF.prim_to_cons(cfg, W), 40)
     assert np.all(max_rel_field(oracle_shape(cfg, U), R) <= 1e-10)
+
+
+def sides_cfg(ndim, n, order, bc):
+    return dict(BASE, ndim=ndim, n=n, cloud_radius=0.3, ramp_delta=0.015, ramp_width=0.1, weno_order=order, bc=bc,
+                p_inf=1.2e6)
+
+
+@pytest.mark.parametrize("ndim,n", [(3, 20), (3, 33), (1, 70)])
+@pytest.mark.parametrize("order", [5, 3])
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+def test_periodic_sides(ctx, ndim, n, order, precision):
+    """A moving state on a periodic domain that no tile divides, in chunks of a
+    plane or two that reach across the sides, against the oracle: the FP64
+    and FP32 bars."""
+    say("periodic", ndim, n, order, precision)
+    cfg = sides_cfg(ndim, n, order, "periodic")
+    W = random_smooth_primitives(ndim, n, seed=21 + n)
+    steps = 12
+    U, _, dts = gpu_run(ctx, cfg, precision, W=W, n_steps=steps)
+    R, rdts = OF.run_steps(cfg, OF.prim_to_cons(cfg, W), steps)
+    if precision == "f64":
+        np.testing.assert_allclose(dts, rdts, rtol=1e-12)
+        assert np.all(max_rel_field(oracle_shape(cfg, U), R) <= 1e-10)
+    else:
+        assert np.all(rel_l1(oracle_shape(cfg, U), R) <= 1e-4)
+
+
+@pytest.mark.parametrize("precision,ndim,n", [("f32", 3, 20), ("f32", 3, 48), ("f64", 3, 20), ("f64", 3, 40),
+                                              ("f32", 2, 45), ("f64", 2, 100), ("f64", 1, 70)])
+@pytest.mark.parametrize("bc", ["periodic", "characteristic"])
+@pytest.mark.parametrize("order", [5, 3])
+def test_default_tiling_at_other_sides_and_order(precision, ndim, n, bc, order):
+    """Ghost cells of periodic and far-field sides in every chunk: the default
+    tiling's state, step sizes and QoI are those of large tiles, bit for bit."""
+    from paper_1705_04374_amd import capi
+    say("default tiling", precision, ndim, n, bc, order)
+    cfg = sides_cfg(ndim, n, order, bc)
+    W = random_smooth_primitives(ndim, n, seed=5)
+    tune = {1: (256, 1, 1, 2), 2: (16, 14, 1, 2), 3: (16, 16, 16, 2)}[ndim]
+    a = gpu_run(capi.Context(0), cfg, precision, W=W, n_steps=3)
+    b = gpu_run(capi.Context(0), cfg, precision, W=W, n_steps=3, tune=tune)
+    assert np.array_equal(a[0], b[0])
+    assert a[1] == b[1]
+    assert np.array_equal(a[2], b[2])
 
 
 # --------------------------------------------------------------------------
