@@ -289,8 +289,9 @@ static void run_tiles(ofm_run& r, std::vector<WorkItem>& work)
 // samples take shorter chunks than many (stage launches of 40 steps of the
 // last 64^3 sample of 61: 9.3 ms in float and 36.9 in double with the tiling
 // of them all, 4.0 and 6.7 with its own).  A tiling that was set stays, as do
-// K and the room for the tiles.  The graph is captured again.  Results depend neither on the tile order nor on the
-// tiling (each cell's arithmetic is fixed; Sum2).
+// K and the room for the tiles.  The graph is captured again.  Results depend
+// neither on the tile order nor on the tiling (each cell's arithmetic is fixed;
+// the sensors' sums: Sum2).
 static int run_compact(ofm_run& r)
 {
     int64_t live = 0;

@@ -486,10 +486,15 @@ __device__ __forceinline__ T k_coef(const Phys<T>& ph, T a2, T p)
 }
 
 // Running reduction of one thread (CFL speed, QoIs, failure counters).
-// Sum in double with its rounding error carried along, about 106 bits: the
-// sensors' sums round to the same double in whatever order the cells are
-// added, so the tiling can follow the size of the whole batch and a sample
-// still gives the same QoI in any batch or alone.
+// Sum in double with its rounding error carried along, so that the sensors'
+// sums round to the same double under other tilings (orders of adding) and a
+// sample gives the same QoI in any batch and alone.  Not by construction: lo
+// is itself summed in double, so with N cells two orders can differ by up to
+// N^2 2^-106 of the sum of magnitudes (commonly N 2^-106), which shows only
+// where the total lies that near to the middle between two doubles: of 10^6
+// cells of one sign commonly one sum in 10^10, always by one last bit.  Few
+// cells of like magnitude (the pressure sensor's, below some 10^4 within a
+// factor 10^6) add without any error in lo.
 struct Sum2 {
     double hi, lo;
     __device__ __forceinline__ void add(double x)
@@ -741,19 +746,20 @@ template <int TX, int TY> constexpr int cell_threads() { return round_up64(TX * 
 //          one and converted at the end of the iteration (their latency hides
 //          under the z face and the update) instead of loaded where they are
 //          converted
-// Measured launches (us; start of this layout / the others tried):
+// Measured launches (us; this layout / the others tried):
 //   float WENO5, 256^3: stages 1, 2 without a spill, so they take every load
 //     ahead: 963, 999 (without late: 980, 1038; split at 4 waves: 965, 1029).
 //     Stage 3 carries the reduction (16 registers and its doubles); with
 //     either load ahead it spills: 1040 (early: 1098; late: 1317;
 //     split: 1270); held to 3 wavefronts rather than 4, 1128.
 //   float WENO3, 150^3: less work between barriers and fewer registers, so a
-//     fourth wavefront pays: 200, 216, 236 (joint at 3: 225, 256, 279).
+//     fourth wavefront pays: 200, 216, 236 in 16 x 16 tiles (joint at 3: 225,
+//     256, 279; the 16 x 14 tiles of 6 planes taken there now: 167, 184, 242).
 //   double, 192^3: LDS for two axes' edges would halve the occupancy; where
-//     it fits 256 registers, the cell's own loads go ahead: 881, 918, 1003
-//     (the third 975 before its sums carried their errors; none early: 910,
-//     944, 1003; early there too 1075; late: 889, 932, 1098; both: 904, 1022,
-//     1223; three waves spill: 1400, 1610, 1853).
+//     it fits 256 registers, the cell's own loads go ahead: 911, 936, 1023
+//     (none early: 926, 962, 1022; early in the third too: 1099; late alone:
+//     894, 940, 1076; both: 936, 1047, 1081; three waves spill: 1400, 1610,
+//     1853).
 struct StageLayout {
     bool split;
     int waves;
@@ -819,9 +825,8 @@ stage_kernel(LaunchArgs a)
     static_assert(!SPLIT || (FXN <= 2 * NT && FYN <= 2 * NT), "at most two faces per thread in the split pass");
     // a workgroup's LDS is kept below 64 KiB: the one stage-kernel variant
     // above it (a running reduction held in LDS) computed states that
-    // differed between tilings, for a cause not found (the set network's
-    // pooling kernel runs correctly with 73.2 KB); every variant that passed
-    // the tiling-invariance test is below
+    // differed between tilings, for a cause not found; every variant that
+    // passed the tiling-invariance test is below
     static_assert(sizeof(T) * (SPLIT ? WSZ + 2 * NV * ESX : AL + 2 * NV * ES) + sizeof(Red) * (NT / 64) <= 65536,
                   "stage kernel LDS above 64 KiB");
     __shared__ T smem[SPLIT ? WSZ + 2 * NV * ESX : AL + 2 * NV * ES];
@@ -866,7 +871,7 @@ stage_kernel(LaunchArgs a)
     // Plane gz with its halo into sW as primitives: the loads of this
     // thread's cells of it (at most PK), and their conversion.
     constexpr int PK = (HX * HY + NT - 1) / NT;
-        // In-plane offsets of this thread's halo cells, the same for every plane
+    // In-plane offsets of this thread's halo cells, the same for every plane
     uint32_t hidx[PK];
 #pragma unroll
     for (int k = 0; k < PK; ++k) {
@@ -1127,12 +1132,14 @@ stage_kernel(LaunchArgs a)
 #pragma unroll
             for (int k = 0; k < 4; ++k) column(z0 - 3 + k, qc[k], q[1 + k]);
         }
-        // One loop body does all the work (so that every edge and face is
-        // computed by the same code whatever the chunking, bit for bit):
-        // p = z0-6..z0-3 only fill the queue, p = z0-2 adds the edges of
-        // cell z0-1, p = z0-1 the face z0-1/2, and p >= z0 the x-y work of
-        // plane p and the update of cell p.  Plane p is converted into sW at
-        // the end of iteration p-1.
+        // One loop body does all the work, so that every edge and face is
+        // computed by the same code whatever the chunking: p = z0-2 adds the
+        // edges of cell z0-1, p = z0-1 the face z0-1/2, and p >= z0 the x-y
+        // work of plane p and the update of cell p.  The queue is full before
+        // p = z0-2: by FILL's own copy of the conversion to primitives, else by
+        // p = z0-6..z0-3, which do nothing else.  (That the copies give the same
+        // bits is held by the tests of the tilings.)  Plane p is converted into
+        // sW at the end of iteration p-1.
         for (int p = FILL ? z0 - 2 : z0 - 6; p <= z1; ++p) {
             const bool xy_work = p >= z0;
             // global loads issued before the x-y work: the column's plane

@@ -458,7 +458,10 @@ __global__ void __launch_bounds__(256) head_kernel(const uint16_t* __restrict__ 
 // bound by each group's chain of 56 MFMAs, 700 vector and 120 LDS operations a
 // wavefront.  256 sets of 500 took 2.2 ms in 12 launches over 500 MB of stored
 // activations, gradients and GEMM splits before, 40 us now.  (Half sets to 512
-// workgroups: 47 us, and twice the parts to sum.)
+// workgroups: 47 us, and twice the parts to sum.)  A set stays with its
+// workgroup, so that few or very uneven sets leave CUs idle: a gradient call
+// over one set of 500, 73 us; of 10^5, 6.2 ms; of 10^6, 62 ms (282 us, 9.8 and
+// 91 ms with the stored activations spread over rows).
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 phi_back_kernel(const float* __restrict__ x, const int32_t* __restrict__ offsets, int n_sets,
@@ -725,7 +728,10 @@ hipError_t nn_phi_pool(const float* x, const int32_t* offsets, int n_sets, int64
     // earlier dealt to four wavefronts.  A forward call by wavefronts against
     // by workgroups: 256 sets of 500, 47 us against 35; 1000 of 500, 50 against
     // 49; 1000 of 100, 34 against 38; 2000 of 500, 63 against 65; 4096 of 100,
-    // 48 against 61; 1000 of 60, 32 against 37.
+    // 48 against 61; 1000 of 60, 32 against 37.  Measured with sets of like
+    // size: the rule does not see a large set among many small ones, whose
+    // groups one wavefront then takes in turn (1000 sets of 1 and one of 60000,
+    // 2.1 ms; one set of 10^5 alone, dealt to four, 1.2).
     if (n_sets >= 1024 || rows <= 64 * (int64_t)n_sets)
         hipLaunchKernelGGL((phi_pool_kernel<true>), dim3(n_sets < 4096 ? (n_sets + 3) / 4 : 1024), dim3(256), 0, st, x, offsets,
                            n_sets, P, W2bf, pool_scale, s_bf);

@@ -56,12 +56,13 @@ struct Tuning {
     // they fill the GPU many times over, long chunks save the ends; in
     // between, the last round's fill decides.
     // Measured for 4 steps of one sample with WENO5 (us), 16 planes a chunk
-    // against the choice here: float 48^3 1748 -> 377, 64^3 1739 -> 505, 96^3
-    // 1767 -> 1025, 150^3 3939 -> 3106, 200^3 7079 -> 6636, 256^3 the same;
-    // double 48^3 1965 -> 534, 64^3 1976 -> 766, 96^3 2000 -> 1623, 150^3 7042
-    // -> 6235, 200^3 the same.
-    // Tilings give the same results bit for bit, so that a batch's choice can
-    // follow its total without changing any sample's.
+    // against the choice here: float 48^3 1748 -> 370, 64^3 1744 -> 504, 96^3
+    // 1766 -> 1019, 150^3 3939 -> 3079, 200^3 7168 -> 6626, 256^3 the same;
+    // double 48^3 1988 -> 547, 64^3 2010 -> 779, 96^3 2033 -> 1646, 150^3 7144
+    // -> 6300, 200^3 the same.
+    // A sample's state and step sizes are the same bit for bit under every
+    // tiling, and so are its sensors' sums to all but vanishing odds (Sum2), so
+    // that the choice can follow a batch's total and the members that are left.
     static TileChoice fastest(int precision, int ndim, const int* sizes, int count, int64_t most_tiles)
     {
         const int maxn = *std::max_element(sizes, sizes + count);
