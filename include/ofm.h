@@ -314,7 +314,8 @@ typedef struct ofm_tune_result {
 
 /* The tile and schedule that a solve of one sample of (precision, ndim, n)
  * uses now (the entry ofm_tune_set / ofm_autotune stored, or the default,
- * which in a batch follows the members not yet finished); out [host] receives tx, ty, zchunk, graph_steps (stage_ms_per_step 0, candidates 0). */
+ * which in a batch follows the members not yet finished); out [host] receives
+ * tx, ty, zchunk, graph_steps (stage_ms_per_step 0, candidates 0). */
 int ofm_tune_get(const ofm_ctx* ctx, int32_t precision, int32_t ndim, int32_t n, ofm_tune_result* out);
 
 /* Measure every compiled tile shape (and, in 3-D, z-chunks of 8, 16, 32 and

@@ -752,9 +752,11 @@ template <int TX, int TY> constexpr int cell_threads() { return round_up64(TX * 
 //     Stage 3 carries the reduction (16 registers and its doubles); with
 //     either load ahead it spills: 1040 (early: 1098; late: 1317;
 //     split: 1270); held to 3 wavefronts rather than 4, 1128.
-//   float WENO3, 150^3: less work between barriers and fewer registers, so a
-//     fourth wavefront pays: 200, 216, 236 in 16 x 16 tiles (joint at 3: 225,
-//     256, 279; the 16 x 14 tiles of 6 planes taken there now: 167, 184, 242).
+//   float WENO3, 256^3: less work between barriers and fewer registers, so a
+//     fourth wavefront pays in stages 1, 2: 708, 787 (joint at 3 before: 784,
+//     860).  Stage 3 with the split pass spills 29 registers: 944 (split at 3:
+//     884; joint at 3: 804); joint, 774.  150^3 166, 182, 213 (split there too:
+//     241).
 //   double, 192^3: LDS for two axes' edges would halve the occupancy; where
 //     it fits 256 registers, the cell's own loads go ahead: 911, 936, 1023
 //     (none early: 926, 962, 1022; early in the third too: 1099; late alone:
@@ -770,8 +772,8 @@ template <typename T, int ND, int TY, int STAGE, int ORD> constexpr StageLayout 
     if (ND == 2 && sizeof(T) == 8 && TY <= 8) return { false, 2, false, false };   // for small grids: both axes at once
     if (sizeof(T) == 8) return { true, 2, STAGE < 2, false };
     if (ND < 3) return { false, 3, false, false };
-    if (ORD == 3) return { true, 4, false, false };
-    return STAGE < 2 ? StageLayout{ false, 3, true, true } : StageLayout{ false, 4, false, false };
+    if (STAGE == 2) return { false, 4, false, false };
+    return ORD == 3 ? StageLayout{ true, 4, false, false } : StageLayout{ false, 3, true, true };
 }
 
 // Threads of the stage kernel.  Below three dimensions a launch is one plane
