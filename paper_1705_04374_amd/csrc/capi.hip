@@ -258,13 +258,11 @@ static int run_capture(ofm_run& r)
 }
 
 // Descriptors of the samples that are not done (all before the first step)
-// under the run's tiling, and its work list: larger samples first, tiles of a
-// sample contiguous (a run of one sample needs none).
-static void run_tiles(ofm_run& r, std::vector<WorkItem>& work)
+// under the run's tiling.
+static void run_tile(ofm_run& r)
 {
     int tiles = 0;
     r.most_tiles = 0;
-    work.clear();
     for (size_t i = 0; i < r.mem.size(); ++i) {
         if (r.state[i].done) continue;
         const Member& m = r.mem[i];
@@ -272,14 +270,22 @@ static void run_tiles(ofm_run& r, std::vector<WorkItem>& work)
         tiles += r.desc[i].ntiles;
         r.most_tiles = std::max(r.most_tiles, r.desc[i].ntiles);
     }
+    r.la.n_work = tiles;
+    r.la.zchunk = r.tc.zchunk;
+}
+
+// Their work list: larger samples first, tiles of a sample contiguous (a run
+// of one sample needs none).
+static std::vector<WorkItem> run_list(const ofm_run& r)
+{
+    std::vector<WorkItem> work;
     if (r.mem.size() > 1) {
-        work.reserve(tiles);
+        work.reserve(r.la.n_work);
         for (int i : r.order)
             if (!r.state[i].done)
                 for (int t = 0; t < r.desc[i].ntiles; ++t) work.push_back(WorkItem{ i, t });
     }
-    r.la.n_work = tiles;
-    r.la.zchunk = r.tc.zchunk;
+    return work;
 }
 
 // Once the tiles of finished samples are more than a tenth of the work list:
@@ -304,16 +310,19 @@ static int run_compact(ofm_run& r)
     if (live == 0 || (double)live > 0.9 * (double)r.la.n_work) return OFM_OK;
     ofm_ctx* ctx = r.ctx;
     const ofm_solve_spec& s0 = r.mem[0].spec;
-    std::vector<WorkItem> work;
     const TileChoice before = r.tc;
+    r.la.n_work = (int)live;
     if (!r.tuned) r.tc = Tuning::fastest(s0.precision, s0.ndim, sizes.data(), (int)sizes.size(), r.room);
-    run_tiles(r, work);
-    if (r.la.n_work > r.room) {             // (no tiling that fits is among the choices)
-        r.tc = before;
-        run_tiles(r, work);
+    if (r.tc.tx != before.tx || r.tc.ty != before.ty || r.tc.zchunk != before.zchunk) {
+        run_tile(r);
+        if (r.la.n_work > r.room) {         // (no tiling that fits is among the choices)
+            r.tc = before;
+            run_tile(r);
+        }
+        HIPCHK(ctx, hipMemcpyAsync(r.d_desc, r.desc.data(), sizeof(SampleDesc) * r.desc.size(), hipMemcpyHostToDevice,
+                                   ctx->stream));
     }
-    HIPCHK(ctx, hipMemcpyAsync(r.d_desc, r.desc.data(), sizeof(SampleDesc) * r.desc.size(), hipMemcpyHostToDevice,
-                               ctx->stream));
+    const std::vector<WorkItem> work = run_list(r);
     HIPCHK(ctx, hipMemcpyAsync(r.d_work, work.data(), sizeof(WorkItem) * work.size(), hipMemcpyHostToDevice,
                                ctx->stream));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
@@ -357,8 +366,8 @@ static int run_begin(ofm_ctx* ctx, ofm_run& r, bool init, int64_t dts_len, hipSt
     r.desc.assign(ns, SampleDesc{});
     r.state.resize(ns);
     for (SampleState& s : r.state) memset(&s, 0, sizeof s);
-    std::vector<WorkItem> work;
-    run_tiles(r, work);
+    run_tile(r);
+    const std::vector<WorkItem> work = run_list(r);
     const int tiles = r.la.n_work;
     r.room = tiles;
 
