@@ -83,12 +83,18 @@ struct Tuning {
             return t;
         }
         if (ndim == 2) {
-            // double: 16 x 8 tiles up to two a CU, whose workgroups take both
-            // axes at once, then 16 x 14, which redo less of their halos
-            // (4 steps, us: 64^2 218 against 233, 256^2 255 and 285, 320^2
-            // 345 and 291).  float: 16 x 16 where that saves a second tile a
-            // CU (256^2 218 against 236; 160^2 216 and 211, 320^2 252 and 237).
-            if (dbl) t.ty = tiles(16, 8, 1) <= std::min<int64_t>(2 * kCUs, most_tiles) ? 8 : 14;
+            // double: 16 x 8 tiles, whose workgroups take both axes at once, up
+            // to one a CU, and up to two where the 16 x 14 ones, which redo less
+            // of their halos, would be more than one too (4 steps, us, 16 x 8
+            // against 16 x 14: 100^2 233 and 244, 176^2 235 and 251; 192^2 261
+            // and 252, 224^2 263 and 252; 240^2 266 and 293, 256^2 266 and 294;
+            // 272^2 317 and 295).  float: 16 x 16 where that saves a second
+            // tile a CU (256^2 218 against 236; 160^2 216 and 211, 320^2 252
+            // and 237).
+            if (dbl) {
+                const int64_t t8 = tiles(16, 8, 1);
+                t.ty = t8 <= most_tiles && (t8 <= kCUs || (t8 <= 2 * kCUs && tiles(16, 14, 1) > kCUs)) ? 8 : 14;
+            }
             else t.ty = tiles(16, 16, 1) <= kCUs && tiles(16, 14, 1) > kCUs ? 16 : 14;
             return t;
         }

@@ -11,6 +11,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 DRIVER = r"""
 #include "tuning.h"
 #include <cstdio>
+#include <utility>
 using namespace ofm;
 
 static int64_t tiles(const TileChoice& t, int nd, const int* n, int count)
@@ -56,6 +57,10 @@ int main()
                 if (t.tx != g.tx || t.ty != g.ty || t.zchunk != g.zchunk) { ++bad; printf("bad: n %d\n", n); }
             }
         }
+    // 2-D double: as many CUs as 16 x 8 tiles, then as 16 x 14 tiles, then two
+    // 16 x 8 tiles each; then whichever redoes less
+    for (auto [n, ty] : { std::pair(64, 8), { 176, 8 }, { 192, 14 }, { 224, 14 }, { 240, 8 }, { 256, 8 }, { 272, 14 }, { 1024, 14 } })
+        if (tuning.choose(1, 2, &n, 1).ty != ty) { ++bad; printf("bad: 2-D double %d\n", n); }
     printf("%ld choices, %ld held to their limit, %ld bad\n", all, held, bad);
     return bad != 0;
 }
