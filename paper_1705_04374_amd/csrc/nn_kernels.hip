@@ -460,7 +460,7 @@ __global__ void __launch_bounds__(256) head_kernel(const uint16_t* __restrict__ 
 // activations, gradients and GEMM splits before, 40 us now.  (Half sets to 512
 // workgroups: 47 us, and twice the parts to sum.)  A set stays with its
 // workgroup, so that few or very uneven sets leave CUs idle: a gradient call
-// over one set of 500, 73 us; of 10^5, 6.2 ms; of 10^6, 62 ms (282 us, 9.8 and
+// over one set of 500, 73 us; of 10^5, 6.4 ms; of 10^6, 64 ms (282 us, 9.8 and
 // 91 ms with the stored activations spread over rows).
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
@@ -475,6 +475,10 @@ phi_back_kernel(const float* __restrict__ x, const int32_t* __restrict__ offsets
     __shared__ float4 sX[64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lc = lane & 31, half = lane >> 5, n = wave * 32 + lc;
+    // groups of this workgroup's sets, up to 65 (the other loads hide these)
+    int total = 0;
+    for (int set = blockIdx.x + lane * gridDim.x; set < n_sets; set += 64 * gridDim.x)
+        total += min((offsets[set + 1] - offsets[set] + 63) >> 6, 65);
     bf16x8 w2[8], w2t[8];                               // W2 row n; W2 column n
     stage_weights(W2bf, smem, tid);
     __syncthreads();
@@ -496,129 +500,164 @@ phi_back_kernel(const float* __restrict__ x, const int32_t* __restrict__ offsets
 #pragma unroll
     for (int q = 0; q < 4; ++q) dW2[q] = splat16(0.f);
     float db2 = 0.f, db1 = 0.f, dw1[4] = { 0.f, 0.f, 0.f, 0.f };
-    for (int set = blockIdx.x; set < n_sets; set += gridDim.x) {
-        const int r0 = offsets[set], r1 = offsets[set + 1];
-        const float dsc = pool_scale * ds[(int64_t)set * 128 + n];
-        const uint32_t dlo = to_bf16(dsc), dhi = dlo << 16;
-        float xn[2][2];                                 // inputs of the next 64 bubbles
-        auto load = [&](int c) {
+    // The sums so far, added to this workgroup's part: at the end, and after
+    // each 64 groups before it (a float sum over all bubbles of a large set, one
+    // after another, loses digits: 1e-3 of W1's gradient at 3 x 10^5 like ones,
+    // 1e-5 in blocks of 4096).
+    int groups = 0;
+    bool begun = false;
+    auto add = [&](float* p, float v) { *p = begun ? *p + v : v; };
+    auto store = [&]() {
+        // (the empty statement: addresses not worked out ahead of the groups and
+        // held over them)
+        float* g = part + (int64_t)blockIdx.x * NN_PART_PHI;
+        uint32_t at = NN_W2 + (wave * 32 + 4 * half) * 128 + lc;
+        asm volatile("" : "+s"(g), "+v"(at));
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int r = c + i * 32 + lc;
+        for (int kb = 0; kb < 4; ++kb) {
 #pragma unroll
-                for (int k = 0; k < 2; ++k) xn[i][k] = r < r1 ? x[(int64_t)r * 4 + 2 * k + half] : 0.f;
-            }
-        };
-        load(r0);
-        for (int c = r0; c < r1; c += 64) {
-            float xb[2][2];
+            for (int e = 0; e < 16; ++e) add(&g[at + mfma_row(e, 0) * 128 + kb * 32], dW2[kb][e]);
+            dW2[kb] = splat16(0.f);
+        }
+        db2 += __shfl_xor(db2, 32, 64);
+        db1 += __shfl_xor(db1, 32, 64);
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+        for (int k = 0; k < 4; ++k) dw1[k] += __shfl_xor(dw1[k], 32, 64);
+        if (half == 0) {
+            add(&g[NN_B2 + n], db2);
+            add(&g[NN_B1 + n], db1);
 #pragma unroll
-                for (int k = 0; k < 2; ++k) xb[i][k] = xn[i][k];
-            load(c + 64);
-            __syncthreads();                            // the pass before has read sX, sH, sT and sD
-            if (wave == 0)
+            for (int k = 0; k < 4; ++k) add(&g[NN_W1 + n * 4 + k], dw1[k]);
+        }
+        db2 = db1 = 0.f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) dw1[k] = 0.f;
+        begun = true;
+        groups = 0;
+    };
+    auto all_sets = [&](auto many_c) {
+        for (int set = blockIdx.x; set < n_sets; set += gridDim.x) {
+            const int r0 = offsets[set], r1 = offsets[set + 1];
+            const float dsc = pool_scale * ds[(int64_t)set * 128 + n];
+            const uint32_t dlo = to_bf16(dsc), dhi = dlo << 16;
+            float xn[2][2];                                 // inputs of the next 64 bubbles
+            auto load = [&](int c) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int r = c + i * 32 + lc;
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) xn[i][k] = r < r1 ? x[(int64_t)r * 4 + 2 * k + half] : 0.f;
+                }
+            };
+            load(r0);
+            for (int c = r0; c < r1; c += 64) {
+                float xb[2][2];
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
 #pragma unroll
-                    for (int k = 0; k < 2; ++k) reinterpret_cast<float*>(&sX[i * 32 + lc])[2 * k + half] = xb[i][k];
-            uint32_t on1 = 0;                           // bit 16 i + e: z1 > 0
+                    for (int k = 0; k < 2; ++k) xb[i][k] = xn[i][k];
+                load(c + 64);
+                __syncthreads();                            // the pass before has read sX, sH, sT and sD
+                if (wave == 0)
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                floatx16 d, dt = splat16(bn1);
+                    for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) d[e] = bias1[e];
+                        for (int k = 0; k < 2; ++k) reinterpret_cast<float*>(&sX[i * 32 + lc])[2 * k + half] = xb[i][k];
+                uint32_t on1 = 0;                           // bit 16 i + e: z1 > 0
 #pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    d = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[k], xb[i][k], d, 0, 0, 0);      // [unit][bubble]
-                    dt = __builtin_amdgcn_mfma_f32_32x32x2f32(xb[i][k], b1[k], dt, 0, 0, 0);    // [bubble][unit]
-                }
+                for (int i = 0; i < 2; ++i) {
+                    floatx16 d, dt = splat16(bn1);
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    u32x4 p;
+                    for (int e = 0; e < 16; ++e) d[e] = bias1[e];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        p.v[q] = pack_bf16(relu(d[8 * t + 2 * q]), relu(d[8 * t + 2 * q + 1]));
-                    *reinterpret_cast<u32x4*>(&sH[(i * 32 + lc) * HP + wave * 32 + t * 16 + half * 8]) = p;
-                }
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    u32x2 p;
-#pragma unroll
-                    for (int q = 0; q < 2; ++q)
-                        p.v[q] = pack_bf16(relu(dt[4 * g + 2 * q]), relu(dt[4 * g + 2 * q + 1]));
-                    *reinterpret_cast<u32x2*>(&sT[n * RP + i * 32 + 16 * (g >> 1) + 8 * half + 4 * (g & 1)]) = p;
-                }
-#pragma unroll
-                for (int e = 0; e < 16; ++e) on1 |= dt[e] > 0.f ? 1u << (16 * i + e) : 0u;
-            }
-            __syncthreads();
-            floatx16 z[2] = { splat16(0.f), splat16(0.f) };
-#pragma unroll
-            for (int t = 0; t < 8; ++t)
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-                    z[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(&sH[(i * 32 + lc) * HP + t * 16 + half * 8]), w2[t],
-                                                                  z[i], 0, 0, 0);
-            int count = 0;
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    u32x4 af;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int e = 8 * t + 2 * q, row = i * 32 + mfma_row(e, lane);
-                        const bool p0 = z[i][e] + bn2 > 0.f && c + row < r1;
-                        const bool p1 = z[i][e + 1] + bn2 > 0.f && c + row + 1 < r1;
-                        count += (p0 ? 1 : 0) + (p1 ? 1 : 0);
-                        sD[row * HP + n] = (uint16_t)(p0 ? dlo : 0u);
-                        sD[(row + 1) * HP + n] = (uint16_t)(p1 ? dlo : 0u);
-                        af.v[q] = (p0 ? dlo : 0u) | (p1 ? dhi : 0u);
+                    for (int k = 0; k < 2; ++k) {
+                        d = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[k], xb[i][k], d, 0, 0, 0);      // [unit][bubble]
+                        dt = __builtin_amdgcn_mfma_f32_32x32x2f32(xb[i][k], b1[k], dt, 0, 0, 0);    // [bubble][unit]
                     }
 #pragma unroll
-                    for (int kb = 0; kb < 4; ++kb)
-                        dW2[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                            __builtin_bit_cast(bf16x8, af), frag(&sT[(kb * 32 + lc) * RP + i * 32 + t * 16 + half * 8]),
-                            dW2[kb], 0, 0, 0);
-                }
-            db2 += count ? dsc * (float)count : 0.f;    // dsc may be infinite or NaN (a label that is)
-            __syncthreads();
+                    for (int t = 0; t < 2; ++t) {
+                        u32x4 p;
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                floatx16 dh = splat16(0.f);
+                        for (int q = 0; q < 4; ++q)
+                            p.v[q] = pack_bf16(relu(d[8 * t + 2 * q]), relu(d[8 * t + 2 * q + 1]));
+                        *reinterpret_cast<u32x4*>(&sH[(i * 32 + lc) * HP + wave * 32 + t * 16 + half * 8]) = p;
+                    }
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        u32x2 p;
+#pragma unroll
+                        for (int q = 0; q < 2; ++q)
+                            p.v[q] = pack_bf16(relu(dt[4 * g + 2 * q]), relu(dt[4 * g + 2 * q + 1]));
+                        *reinterpret_cast<u32x2*>(&sT[n * RP + i * 32 + 16 * (g >> 1) + 8 * half + 4 * (g & 1)]) = p;
+                    }
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) on1 |= dt[e] > 0.f ? 1u << (16 * i + e) : 0u;
+                }
+                __syncthreads();
+                floatx16 z[2] = { splat16(0.f), splat16(0.f) };
 #pragma unroll
                 for (int t = 0; t < 8; ++t)
-                    dh = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(&sD[(i * 32 + lc) * HP + t * 16 + half * 8]), w2t[t],
-                                                                dh, 0, 0, 0);
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const float d = (on1 >> (16 * i + e)) & 1u ? dh[e] : 0.f;
-                    const float4 xv = sX[i * 32 + mfma_row(e, lane)];
-                    dw1[0] += d * xv.x;
-                    dw1[1] += d * xv.y;
-                    dw1[2] += d * xv.z;
-                    dw1[3] += d * xv.w;
-                    db1 += d;
+                    for (int i = 0; i < 2; ++i)
+                        z[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(&sH[(i * 32 + lc) * HP + t * 16 + half * 8]), w2[t],
+                                                                      z[i], 0, 0, 0);
+                int count = 0;
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        u32x4 af;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const int e = 8 * t + 2 * q, row = i * 32 + mfma_row(e, lane);
+                            const bool p0 = z[i][e] + bn2 > 0.f && c + row < r1;
+                            const bool p1 = z[i][e + 1] + bn2 > 0.f && c + row + 1 < r1;
+                            count += (p0 ? 1 : 0) + (p1 ? 1 : 0);
+                            sD[row * HP + n] = (uint16_t)(p0 ? dlo : 0u);
+                            sD[(row + 1) * HP + n] = (uint16_t)(p1 ? dlo : 0u);
+                            af.v[q] = (p0 ? dlo : 0u) | (p1 ? dhi : 0u);
+                        }
+#pragma unroll
+                        for (int kb = 0; kb < 4; ++kb)
+                            dW2[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                                __builtin_bit_cast(bf16x8, af), frag(&sT[(kb * 32 + lc) * RP + i * 32 + t * 16 + half * 8]),
+                                dW2[kb], 0, 0, 0);
+                    }
+                db2 += count ? dsc * (float)count : 0.f;    // dsc may be infinite or NaN (a label that is)
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    floatx16 dh = splat16(0.f);
+#pragma unroll
+                    for (int t = 0; t < 8; ++t)
+                        dh = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(&sD[(i * 32 + lc) * HP + t * 16 + half * 8]), w2t[t],
+                                                                    dh, 0, 0, 0);
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        const float d = (on1 >> (16 * i + e)) & 1u ? dh[e] : 0.f;
+                        const float4 xv = sX[i * 32 + mfma_row(e, lane)];
+                        dw1[0] += d * xv.x;
+                        dw1[1] += d * xv.y;
+                        dw1[2] += d * xv.z;
+                        dw1[3] += d * xv.w;
+                        db1 += d;
+                    }
                 }
+                if constexpr (decltype(many_c)::value)
+                    if (++groups == 64) store();
             }
         }
-    }
-    float* g = part + (int64_t)blockIdx.x * NN_PART_PHI;
+    };
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) g[NN_W2 + (wave * 32 + mfma_row(e, lane)) * 128 + kb * 32 + lc] = dW2[kb][e];
-    db2 += __shfl_xor(db2, 32, 64);
-    db1 += __shfl_xor(db1, 32, 64);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) dw1[k] += __shfl_xor(dw1[k], 32, 64);
-    if (half == 0) {
-        g[NN_B2 + n] = db2;
-        g[NN_B1 + n] = db1;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) g[NN_W1 + n * 4 + k] = dw1[k];
+    for (int off = 32; off >= 1; off >>= 1) total = min(total + __shfl_xor(total, off, 64), 65);
+    // a loop of its own where they are few: the stores in it cost a call over
+    // 256 sets of 500 4 %
+    if (total > 64) {
+        all_sets(std::true_type{});
+        store();
+    } else {
+        all_sets(std::false_type{});
+        store();
     }
 }
 

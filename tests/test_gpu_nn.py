@@ -291,3 +291,29 @@ def test_gradients_beside_a_label_that_is_not_finite(ctx, bad):
     for k in ("b2", "W2"):
         assert np.isfinite(gg[k][off_units]).all(), k
         assert rel(gg[k][off_units], ref[k][off_units]) <= 1e-3, k
+
+
+@pytest.mark.parametrize("sizes", [[300000], [70, 300000, 129]])
+def test_gradients_of_a_large_set_of_like_bubbles(ctx, sizes):
+    """Sums of 3e5 equal terms: in float one after another they lose up to
+    3e5 2^-25 = 9e-3 (2e4 2^-25 = 6e-4 where a product adds sixteen at once);
+    in blocks of 4096 bubbles, two a lane, (2048 + 74) 2^-25 = 6.3e-5, and as
+    much again for the parts.  Labels far from the outputs, so that the rounding
+    of the pooled sum does not reach the gradients."""
+    import torch
+    say("nn grads, like bubbles", sizes)
+    p, x, off, t = problem(4, sizes)
+    big = sizes.index(300000)
+    x[off[big]:off[big + 1]] = x[off[big]]
+    t = 1e4 * t
+    scale = float(np.float32(1.0 / 300000))
+    net = gpu_net(ctx, p, scale)
+    g = torch.zeros(N.param_count(), dtype=torch.float32, device="cuda")
+    loss = torch.zeros(1, dtype=torch.float32, device="cuda")
+    net.grads(dev(x), dev(off), dev(t), g, loss)
+    _, ref = N.loss_and_grads(p, x, off, scale, t, bf16_ops=True)
+    gg = N.unflatten(g.cpu().numpy().astype(np.float64))
+    for k in ("W1", "b1", "W2", "b2"):
+        e = rel(gg[k], ref[k])
+        say("  %s %.2e" % (k, e))
+        assert e <= 1.3e-4, (k, e)
